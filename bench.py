@@ -10,8 +10,8 @@ central-Hermite transform, relaxation, inverse transform, store), one kernel
 launch.  The library runs steps in place on one population array and
 alternates two kernels: the streaming step (neighbour slots) and the local
 step (own slots); both move the same algorithmic bytes.  The timed steps are
-replayed from HIP graphs of 64, 32, ..., 2 steps (the longest that fit),
-built before the timed region.
+replayed from a HIP graph of 64 steps, built before the timed region; the
+steps left over are launched one by one.
 
 Prints one JSON line.  value = fluid-cell MLUPS over the timed steps, with
 all state resident in HBM.  roofline.achieved = algorithmic bytes per launch
@@ -96,7 +96,7 @@ def time_steps(capi, torch, cfg, storage, steps, warmup, stream, feq_order=6):
     info = d.info()
     if warmup:
         d.step(warmup)
-    d.prepare_steps()  # the step graphs are built before the timed region
+    d.prepare_steps()  # the step graph is built before the timed region
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()

@@ -231,7 +231,7 @@ class Domain:
         return lbm_step_wait(self.h)
 
     def prepare_steps(self):
-        """Build the step graphs now (outside a timed run)."""
+        """Build the step graph now (outside a timed run)."""
         check(lbm_prepare_steps(self.h))
 
     def moments(self):

@@ -5,8 +5,8 @@
 // contain updated cells, and for tiles that touch a wall, inlet, box face or
 // non-updated cell a 32-bit link mask per cell.  Interior tiles (every cell
 // updated, every link a plain pull after periodic wrap) carry no mask and
-// take the kernels' branch-free path.  Runs of steps are replayed from HIP
-// graphs built node by node.
+// take the kernels' branch-free path.  Long runs of steps are replayed from
+// a HIP graph built node by node, short ones launched step by step.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -229,10 +229,17 @@ void build_tiles(const uint8_t *flags, int nx, int ny, int nz, unsigned per, con
     }
 }
 
-// Step graphs: one per length 64, 32, ..., 2 steps (even lengths end in the
-// phase they start in); a run of n steps replays the longest that fit.
-constexpr int kGraphSizes = 6;
-constexpr int graph_len(int j) { return 64 >> j; }
+// Step graph: 64 steps (an even length ends in the phase it starts in).
+// Below 64 steps a replay is never faster than launching the steps one by
+// one (32^3 FP32: 8 steps 83 us against 68, 32 steps 182 against 167, 64
+// steps 310 against 299; a 128^3 box runs the same either way, its kernels
+// being longer than a launch).  Long runs gain from replays where the
+// kernels are short (640 steps: 8^3 2246 us against 2352, 32^3 2549 against
+// 2691) and cost the host a third of the time (0.8 us a step against 2.4).
+// Building the graph costs about 100 us of host time, so only a run of at
+// least kGraphBuild steps builds it; any run uses it once it is there.
+constexpr int kGraphSteps = 64;
+constexpr int kGraphBuild = 256;
 
 // Largest population array the buffer-instruction kernels address (their
 // byte offsets are 32-bit); larger arrays take the 64-bit kernels.
@@ -245,6 +252,77 @@ uint64_t array_bytes(uint64_t P, int ny, int nz, int storage)
     const uint64_t es = storage_bytes(storage);
     return (Q * P * es + 18ull * ny * nz * es + 255) / 256 * 256;
 }
+
+// Status words of domains: 4 bytes each of pinned host memory that the step
+// kernels write, so that waiting for steps is one stream synchronisation
+// and a host read, with no copy behind it (one step of a 16^3 box, waited
+// for: 34.8 -> 14.5 us).  The words come from blocks of 1024; a block is
+// given back when none of its words is in use and another block is left.
+struct StatusWord {
+    uint32_t *host = nullptr, *dev = nullptr;
+};
+
+struct StatusBlock {
+    uint32_t *host = nullptr, *dev = nullptr;
+    std::vector<uint32_t> unused;
+};
+constexpr uint32_t kStatusBlockWords = 1024;
+std::mutex g_status_mutex;
+std::vector<StatusBlock> g_status_blocks;
+
+hipError_t status_alloc(StatusWord &w)
+{
+    std::lock_guard<std::mutex> lock(g_status_mutex);
+    StatusBlock *b = nullptr;
+    for (auto &c : g_status_blocks)
+        if (!c.unused.empty())
+            b = &c;
+    if (!b) {
+        StatusBlock n;
+        void *p = nullptr, *q = nullptr;
+        hipError_t e = hipHostMalloc(&p, kStatusBlockWords * sizeof(uint32_t), hipHostMallocPortable | hipHostMallocMapped);
+        if (e == hipSuccess && (e = hipHostGetDevicePointer(&q, p, 0)) != hipSuccess)
+            (void)hipHostFree(p);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e;
+        }
+        n.host = (uint32_t *)p;
+        n.dev = (uint32_t *)q;
+        for (uint32_t i = 0; i < kStatusBlockWords; ++i)
+            n.unused.push_back(i);
+        g_status_blocks.push_back(std::move(n));
+        b = &g_status_blocks.back();
+    }
+    const uint32_t i = b->unused.back();
+    b->unused.pop_back();
+    w.host = b->host + i;
+    w.dev = b->dev + i;
+    *w.host = 0;
+    return hipSuccess;
+}
+
+void status_free(StatusWord &w)
+{
+    if (!w.host)
+        return;
+    std::lock_guard<std::mutex> lock(g_status_mutex);
+    for (size_t k = 0; k < g_status_blocks.size(); ++k) {
+        StatusBlock &b = g_status_blocks[k];
+        if (w.host < b.host || w.host >= b.host + kStatusBlockWords)
+            continue;
+        b.unused.push_back((uint32_t)(w.host - b.host));
+        if (b.unused.size() == kStatusBlockWords && g_status_blocks.size() > 1) {
+            (void)hipHostFree(b.host);
+            g_status_blocks.erase(g_status_blocks.begin() + (ptrdiff_t)k);
+        }
+        break;
+    }
+    w = StatusWord{};
+}
+
+// What the host knows of a status word once the steps are complete.
+bool status_set(const StatusWord &w) { return __atomic_load_n(w.host, __ATOMIC_ACQUIRE) != 0; }
 
 } // namespace
 
@@ -275,7 +353,7 @@ struct lbm_domain {
     std::vector<uint32_t> h_wall, h_inlm;  // per wall-tile lane: link mask, inlet links
     uint32_t n_inl = 0;                    // inlet tiles
     std::vector<uint64_t> inlet_cells;     // inlet cells, ascending (index = inlet ordinal)
-    uint32_t *d_status = nullptr;
+    StatusWord status;                     // set by a step that goes unstable
     uint64_t ntiles = 0, nwall = 0, n_updated = 0;
     double omega = 1.0, omega_b = 1.0;
     double omega_o[4] = {1.0, 1.0, 1.0, 1.0}; // orders 3..6
@@ -294,8 +372,8 @@ struct lbm_domain {
     // (past the 4 GiB that buffer instructions reach)
     bool wide() const { return force_wide || bytes > kNarrowBytes; }
     bool unstable = false;
-    hipGraphExec_t graph[kGraphSizes] = {};   // graph j runs graph_len(j) steps from phase 0
-    hipGraph_t graph_def[kGraphSizes] = {};
+    hipGraphExec_t graph = nullptr; // kGraphSteps steps from phase 0
+    hipGraph_t graph_def = nullptr;
     bool graph_dirty = true;
     std::vector<TileRec> h_tiles; // host copy of the tile list (batch tables are built from it)
     lbm_batch *batch = nullptr;    // resident in this batch
@@ -370,7 +448,7 @@ KDomain kdomain(const lbm_domain *d)
     k.bzaux = d->d_bzaux;
     k.rowtiles = d->nx % 64 == 0 ? (uint32_t)(d->nx / 64) : 0u;
     k.drow = make_fastdiv(k.rowtiles ? k.rowtiles : 1u);
-    k.status = d->d_status;
+    k.status = d->status.dev;
     k.P = (uint32_t)d->P;
     k.tbytes = (uint32_t)(Q * 64 * storage_bytes(d->storage));
     k.side = d->P / 64 * k.tbytes;
@@ -418,9 +496,7 @@ template <typename F> decltype(auto) dispatch_storage(int st, F &&f)
 int sync_status(lbm_domain *d)
 {
     HIP_TRY(hipStreamSynchronize(d->stream));
-    uint32_t st = 0;
-    HIP_TRY(copy_sync(d->stream, &st, d->d_status, sizeof st, hipMemcpyDeviceToHost));
-    if (st)
+    if (status_set(d->status))
         d->unstable = true;
     return LBM_OK;
 }
@@ -434,14 +510,12 @@ int check_domain(const lbm_domain *d)
 
 void release_graph(lbm_domain *d)
 {
-    for (int j = 0; j < kGraphSizes; ++j) {
-        if (d->graph[j])
-            (void)hipGraphExecDestroy(d->graph[j]);
-        if (d->graph_def[j])
-            (void)hipGraphDestroy(d->graph_def[j]);
-        d->graph[j] = nullptr;
-        d->graph_def[j] = nullptr;
-    }
+    if (d->graph)
+        (void)hipGraphExecDestroy(d->graph);
+    if (d->graph_def)
+        (void)hipGraphDestroy(d->graph_def);
+    d->graph = nullptr;
+    d->graph_def = nullptr;
     d->graph_dirty = true;
 }
 
@@ -462,10 +536,10 @@ void free_domain(lbm_domain *d)
         dfree(s, d->d_bzc);
         dfree(s, d->d_bzaux);
         dfree(s, d->d_stats);
-        dfree(s, d->d_status);
         if (d->own_stream)
             (void)hipStreamDestroy(s);
     }
+    status_free(d->status);
     delete d;
 }
 
@@ -597,6 +671,7 @@ hipError_t normalise(lbm_domain *d)
 }
 
 // f^eq of the given fields (null: rho = 1, u = 0) in every cell, phase 0.
+// The caller waits for the stream and clears the status word then.
 int init_eq(lbm_domain *d, const float *rho_dev, const float *u_dev)
 {
     const KDomain k = kdomain(d);
@@ -608,9 +683,14 @@ int init_eq(lbm_domain *d, const float *rho_dev, const float *u_dev)
     d->phase = 0;
     HIP_TRY(side_refresh(d));
     HIP_TRY(curved_refresh(d));
-    HIP_TRY(hipMemsetAsync(d->d_status, 0, sizeof(uint32_t), d->stream));
-    d->unstable = false;
     return LBM_OK;
+}
+
+// A new state (no step in flight): stable until a step says otherwise.
+void clear_status(lbm_domain *d)
+{
+    *d->status.host = 0;
+    d->unstable = false;
 }
 
 // Cells rounded up to whole 64-cell tiles.
@@ -738,7 +818,7 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     }
     if (!dmalloc((void **)&d->d_flags, ncells) || !dmalloc((void **)&d->d_tiles, T.recs.size() * sizeof(TileRec)) ||
         !dmalloc((void **)&d->d_wall, T.wall.size() * 4) || !dmalloc((void **)&d->d_inlet, T.inlet.size() * 4) ||
-        !dmalloc((void **)&d->d_inlrec, T.inlrec.size() * 4) || !dmalloc((void **)&d->d_status, sizeof(uint32_t)) ||
+        !dmalloc((void **)&d->d_inlrec, T.inlrec.size() * 4) || status_alloc(d->status) != hipSuccess ||
         !dmalloc((void **)&d->d_iterm, (size_t)T.n_inl * Q * 64 * sizeof(float)))
         return bail(fail(LBM_ERR_OOM, "domain tables"));
     auto up = [&](void *dst, const void *src, size_t n) {
@@ -762,6 +842,7 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         rc = fail(LBM_ERR_DEVICE, "initialisation failed");
     if (rc != LBM_OK)
         return bail(rc);
+    clear_status(d);
     *out = d;
     return LBM_OK;
 }
@@ -782,33 +863,25 @@ hipError_t add_kernel_node(hipGraph_t g, hipGraphNode_t prev, const void *func, 
 }
 
 
-// Build (not capture) the step graphs: graph j chains graph_len(j) step
-// nodes starting in phase 0.  Built node by node so that work other threads
-// issue meanwhile cannot interfere.
+// Build (not capture) the step graph: kGraphSteps step nodes in a chain,
+// starting in phase 0.  Built node by node so that work other threads issue
+// meanwhile cannot interfere.
 int build_graph(lbm_domain *d)
 {
     release_graph(d);
     KDomain k = kdomain(d);
     const TileRec *tiles = d->d_tiles;
     uint32_t nt = (uint32_t)d->ntiles;
-    for (int j = 0; j < kGraphSizes; ++j) {
-        hipGraph_t g = nullptr;
-        HIP_TRY(hipGraphCreate(&g, 0));
-        hipGraphNode_t prev = nullptr;
-        for (int s = 0; s < graph_len(j); ++s) {
-            const void *fn = step_kernel(d->storage, d->variant(), (uint32_t)(s & 1), k.rowtiles != 0, d->wide());
-            void *args[] = {&k, &tiles, &nt};
-            hipGraphNode_t node = nullptr;
-            hipError_t e = add_kernel_node(g, prev, fn, step_grid(d), kBlock, args, &node);
-            if (e != hipSuccess) {
-                (void)hipGraphDestroy(g);
-                return fail(LBM_ERR_DEVICE, "graph node: %s", hipGetErrorString(e));
-            }
-            prev = node;
-        }
-        d->graph_def[j] = g;
-        HIP_TRY(hipGraphInstantiate(&d->graph[j], g, nullptr, nullptr, 0));
+    HIP_TRY(hipGraphCreate(&d->graph_def, 0));
+    hipGraphNode_t prev = nullptr;
+    for (int s = 0; s < kGraphSteps; ++s) {
+        const void *fn = step_kernel(d->storage, d->variant(), (uint32_t)(s & 1), k.rowtiles != 0, d->wide());
+        void *args[] = {&k, &tiles, &nt};
+        hipGraphNode_t node = nullptr;
+        HIP_TRY(add_kernel_node(d->graph_def, prev, fn, step_grid(d), kBlock, args, &node));
+        prev = node;
     }
+    HIP_TRY(hipGraphInstantiate(&d->graph, d->graph_def, nullptr, nullptr, 0));
     d->graph_dirty = false;
     return LBM_OK;
 }
@@ -1102,6 +1175,8 @@ int lbm_init_fields(lbm_domain *d, const float *rho, const float *u)
         rc = init_eq(d, dr, du);
     if (rc == LBM_OK && hipStreamSynchronize(d->stream) != hipSuccess)
         rc = fail(LBM_ERR_DEVICE, "initialisation failed");
+    if (rc == LBM_OK)
+        clear_status(d);
     dfree(d->stream, dr);
     dfree(d->stream, du);
     return rc;
@@ -1119,7 +1194,7 @@ int lbm_step_async(lbm_domain *d, int n)
         return fail(LBM_ERR_UNSTABLE, "domain went unstable earlier; re-initialise it");
     if (d->ntiles == 0) // nothing is updated, the state stays as it is
         return LBM_OK;
-    if (n >= 2 && d->graph_dirty)
+    if (n >= kGraphBuild && d->graph_dirty)
         if (int rc = build_graph(d))
             return rc;
     int left = n;
@@ -1130,12 +1205,10 @@ int lbm_step_async(lbm_domain *d, int n)
         --left;
         ++local_steps;
     }
-    for (int j = 0; j < kGraphSizes; ++j) {
-        while (left >= graph_len(j)) {
-            HIP_TRY(hipGraphLaunch(d->graph[j], d->stream));
-            left -= graph_len(j);
-            local_steps += (uint64_t)graph_len(j) / 2;
-        }
+    while (!d->graph_dirty && left >= kGraphSteps) {
+        HIP_TRY(hipGraphLaunch(d->graph, d->stream));
+        left -= kGraphSteps;
+        local_steps += (uint64_t)kGraphSteps / 2;
     }
     while (left > 0) {
         HIP_TRY(launch_step(d, (uint32_t)d->phase));
@@ -1388,10 +1461,10 @@ int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes)
     const char *p = (const char *)buf + kStateHeader;
     if (copy_sync(d->stream, d->buf, p, d->bytes, hipMemcpyHostToDevice) != hipSuccess ||
         copy_sync(d->stream, d->d_bzaux, p + d->bytes, h[3], hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemsetAsync(d->d_status, 0, sizeof(uint32_t), d->stream) != hipSuccess ||
         hipStreamSynchronize(d->stream) != hipSuccess)
         return fail(LBM_ERR_DEVICE, "state upload failed");
     d->phase = (int)(h[5] & 1u);
+    clear_status(d);
     d->unstable = (h[5] >> 1) != 0;
     return LBM_OK;
 }

@@ -109,7 +109,7 @@ struct KDomain {
     const uint8_t *flags;    // cell flags
     const uint32_t *wall;    // link masks of wall tiles, 64 per wall tile
     const float *iterm;      // inlet terms, [27][64] per inlet tile
-    uint32_t *status;        // bit 0: a step went unstable
+    uint32_t *status;        // 1: a step went unstable (pinned host memory, or a batch's device table)
     uint64_t side;           // byte offset of the side rows: 2 x 9 rows of ny * nz elements
     uint32_t P;              // cells rounded up to whole tiles
     uint32_t tbytes;         // bytes of one tile block: 27 x 64 populations
@@ -844,7 +844,7 @@ __device__ __forceinline__ bool plane_step(uint32_t v, int dv, uint32_t n, bool 
 __device__ __forceinline__ void check_state(const KDomain &d, float rho, float ux, float uy, float uz)
 {
     if (!(rho > 0.f) || !(__builtin_fabsf(ux) + __builtin_fabsf(uy) + __builtin_fabsf(uz) < 1e30f))
-        atomicOr(d.status, 1u);
+        __hip_atomic_store(d.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Inlet term of link k of the lane (0 where link k is not an inlet link).
