@@ -18,7 +18,6 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <vector>
 
 #define LBM_HOST_TU
@@ -79,154 +78,6 @@ FastDiv make_fastdiv(uint32_t d)
     f.s2 = l > 0 ? l - 1 : 0;
     f.d = d;
     return f;
-}
-
-bool updated(uint8_t fl) { return fl == LBM_FLUID || fl == LBM_OUTLET; }
-
-// Link classification of one cell (host copy of the boundary rules):
-// returns the wall mask (bit i: halfway bounce-back for population i,
-// kMaskOutlet for an outlet cell, kMaskInlet if any link comes from an inlet
-// cell, kMaskSkip if the cell is not updated) and the inlet mask; src[i]
-// receives the inlet cell of each inlet link.
-void classify_cell(const uint8_t *flags, int nx, int ny, int nz, unsigned per, uint64_t cell, uint32_t &wall,
-                   uint32_t &inl, uint64_t *src = nullptr)
-{
-    wall = 0;
-    inl = 0;
-    const uint8_t self = flags[cell];
-    if (!updated(self)) {
-        wall = kMaskSkip;
-        return;
-    }
-    if (self == LBM_OUTLET)
-        wall |= kMaskOutlet;
-    const int x = (int)(cell % nx), y = (int)((cell / nx) % ny), z = (int)(cell / ((uint64_t)nx * ny));
-    for (int i = 0; i < Q; ++i) {
-        int sx = x - cx(i), sy = y - cy(i), sz = z - cz(i);
-        if (per & 1u)
-            sx = (sx + nx) % nx;
-        if (per & 2u)
-            sy = (sy + ny) % ny;
-        if (per & 4u)
-            sz = (sz + nz) % nz;
-        if (sx >= nx && !(per & 1u) && self == LBM_OUTLET)
-            sx = nx - 1;
-        if (sx < 0 || sx >= nx || sy < 0 || sy >= ny || sz < 0 || sz >= nz) {
-            wall |= 1u << i;
-            continue;
-        }
-        const uint64_t s = ((uint64_t)sz * ny + sy) * nx + sx;
-        const uint8_t fs = flags[s];
-        if (fs == LBM_SOLID) {
-            wall |= 1u << i;
-        } else if (fs == LBM_INLET) {
-            wall |= (1u << i) | kMaskInlet;
-            inl |= 1u << i;
-            if (src)
-                src[i] = s;
-        }
-    }
-}
-
-// Tile list of a domain.  wall: per cell of each wall tile the link mask;
-// inlet: per cell of each wall tile the index of its inlet record (kNoRec
-// if it has no inlet link); inlrec: per record the inlet link mask and 27
-// inlet ordinals (the rank of the link's inlet cell among all inlet cells,
-// kNoRec for other links); n_inl: tiles with an inlet-term block.
-struct Tiles {
-    std::vector<TileRec> recs;
-    std::vector<uint32_t> wall, inlet, inlrec;
-    uint64_t n_updated = 0;
-    uint32_t n_inl = 0;
-};
-
-// Build the tile list in tile order.  Work is split over host threads by
-// contiguous tile ranges and concatenated in order.  inlet_cells: the inlet
-// cells in ascending order (their position is the inlet ordinal).
-void build_tiles(const uint8_t *flags, int nx, int ny, int nz, unsigned per, const std::vector<uint64_t> &inlet_cells,
-                 bool outlets, Tiles &out)
-{
-    const uint64_t ncells = (uint64_t)nx * ny * nz;
-    const uint64_t ntiles = (ncells + 63) / 64;
-    unsigned nth = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-    if (ntiles < 4096)
-        nth = 1;
-    std::vector<Tiles> part(nth);
-    auto work = [&](unsigned p) {
-        const uint64_t t0 = ntiles * p / nth, t1 = ntiles * (p + 1) / nth;
-        Tiles &T = part[p];
-        uint32_t wl[64], il[64], rec[64];
-        uint64_t src[Q];
-        for (uint64_t t = t0; t < t1; ++t) {
-            bool any = false, plain = true;
-            TileRec r{0u, (uint32_t)t, -1, kNoRec, 0u, {0u, 0u}, 0u, 0u, 0u};
-            for (int l = 0; l < 64; ++l) {
-                const uint64_t c = t * 64 + l;
-                rec[l] = kNoRec;
-                if (c >= ncells) {
-                    wl[l] = kMaskSkip;
-                    il[l] = 0;
-                } else {
-                    classify_cell(flags, nx, ny, nz, per, c, wl[l], il[l], src);
-                }
-                if (il[l]) {
-                    rec[l] = (uint32_t)(T.inlrec.size() / kRecWords);
-                    T.inlrec.push_back(il[l]);
-                    for (int i = 0; i < Q; ++i) {
-                        uint32_t ord = kNoRec;
-                        if (il[l] & (1u << i))
-                            ord = (uint32_t)(std::lower_bound(inlet_cells.begin(), inlet_cells.end(), src[i]) -
-                                             inlet_cells.begin());
-                        T.inlrec.push_back(ord);
-                    }
-                }
-                if (!(wl[l] & kMaskSkip)) {
-                    any = true;
-                    T.n_updated++;
-                    r.act[l >> 5] |= 1u << (l & 31);
-                    r.inlm |= il[l];
-                    if (outlets && !(per & 1u) && (c % nx) == (uint64_t)nx - 1)
-                        r.edge = 1u;
-                }
-                if (wl[l])
-                    plain = false;
-            }
-            if (!any)
-                continue;
-            if (!plain) {
-                r.wall = (int32_t)(T.wall.size() / 64);
-                if (r.inlm)
-                    r.inl = T.n_inl++;
-                T.wall.insert(T.wall.end(), wl, wl + 64);
-                T.inlet.insert(T.inlet.end(), rec, rec + 64);
-            }
-            T.recs.push_back(r);
-        }
-    };
-    std::vector<std::thread> th;
-    for (unsigned p = 1; p < nth; ++p)
-        th.emplace_back(work, p);
-    work(0);
-    for (auto &t : th)
-        t.join();
-    for (unsigned p = 0; p < nth; ++p) {
-        const int32_t off = (int32_t)(out.wall.size() / 64);
-        const uint32_t roff = (uint32_t)(out.inlrec.size() / kRecWords);
-        for (TileRec r : part[p].recs) {
-            if (r.wall >= 0)
-                r.wall += off;
-            if (r.inl != kNoRec)
-                r.inl += out.n_inl;
-            r.ord = (uint32_t)out.recs.size();
-            out.recs.push_back(r);
-        }
-        out.n_inl += part[p].n_inl;
-        out.wall.insert(out.wall.end(), part[p].wall.begin(), part[p].wall.end());
-        for (uint32_t r : part[p].inlet)
-            out.inlet.push_back(r == kNoRec ? kNoRec : r + roff);
-        out.inlrec.insert(out.inlrec.end(), part[p].inlrec.begin(), part[p].inlrec.end());
-        out.n_updated += part[p].n_updated;
-    }
 }
 
 // Step graph: 64 steps (an even length ends in the phase it starts in).
@@ -344,13 +195,14 @@ struct lbm_domain {
     bool stats_on = false;
     uint64_t stats_samples = 0; // local steps accumulated
     uint8_t *d_flags = nullptr;
+    char *d_tables = nullptr; // one allocation: the tile list, wall masks, inlet tables and terms
     TileRec *d_tiles = nullptr;
     uint32_t *d_wall = nullptr, *d_inlet = nullptr, *d_inlrec = nullptr;
     float *d_uin = nullptr;                // [3][n_inlet]
     float *d_iterm = nullptr;              // inlet terms, [27][64] per inlet tile
     float2 *d_bzc = nullptr;               // curved-wall coefficients, [27][64] per wall tile
     float *d_bzaux = nullptr;              // f*_k of the curved links, [27][64] per wall tile
-    std::vector<uint32_t> h_wall, h_inlm;  // per wall-tile lane: link mask, inlet links
+    uint64_t n_inlrec = 0;                 // inlet records
     uint32_t n_inl = 0;                    // inlet tiles
     std::vector<uint64_t> inlet_cells;     // inlet cells, ascending (index = inlet ordinal)
     StatusWord status;                     // set by a step that goes unstable
@@ -375,7 +227,6 @@ struct lbm_domain {
     hipGraphExec_t graph = nullptr; // kGraphSteps steps from phase 0
     hipGraph_t graph_def = nullptr;
     bool graph_dirty = true;
-    std::vector<TileRec> h_tiles; // host copy of the tile list (batch tables are built from it)
     lbm_batch *batch = nullptr;    // resident in this batch
     uint64_t device_bytes = 0;
     uint64_t flags_hash = 0;       // FNV-1a 64 of the creation flags (state images name it)
@@ -527,12 +378,8 @@ void free_domain(lbm_domain *d)
         if (d->own_buffers)
             dfree(s, d->buf);
         dfree(s, d->d_flags);
-        dfree(s, d->d_tiles);
-        dfree(s, d->d_wall);
-        dfree(s, d->d_inlet);
-        dfree(s, d->d_inlrec);
+        dfree(s, d->d_tables);
         dfree(s, d->d_uin);
-        dfree(s, d->d_iterm);
         dfree(s, d->d_bzc);
         dfree(s, d->d_bzaux);
         dfree(s, d->d_stats);
@@ -727,6 +574,83 @@ int scratch_address(int device, float **out)
     return LBM_OK;
 }
 
+} // namespace
+
+#include "lbm_build.inc"
+
+namespace {
+
+// The tables of a new domain from its flags (d->d_flags, host copy in
+// flags), with the population array as scratch memory; d's counts and the
+// hash of the flags.  One host wait, for the counts the tables are
+// allocated by.
+int build_tables(lbm_domain *d, const uint8_t *flags)
+{
+    const KDomain k = kdomain(d);
+    const uint32_t nt = (uint32_t)(d->P / 64), ngroups = (nt + kGroupTiles - 1) / kGroupTiles;
+    const uint64_t hash_groups = d->ncells / kGroupCells, n_inlet = d->inlet_cells.size();
+    const BuildScratch w = build_scratch(d->buf, nt, ngroups, hash_groups, n_inlet);
+    if (w.bytes > d->bytes)
+        return fail(LBM_ERR_STATE, "scratch of %llu bytes exceeds the array", (unsigned long long)w.bytes);
+    const std::vector<uint32_t> cells(d->inlet_cells.begin(), d->inlet_cells.end());
+    HIP_TRY(copy_sync(d->stream, w.inlet_cells, cells.data(), cells.size() * 4, hipMemcpyHostToDevice));
+    const dim3 tiles((nt + 3) / 4);
+    hipLaunchKernelGGL(k_tile_count, tiles, dim3(256), 0, d->stream, k, nt, w.tile, w.nupd);
+    hipLaunchKernelGGL(k_group_count, dim3(ngroups), dim3(kGroupTiles), 0, d->stream, nt, (const uint64_t *)w.tile,
+                       (const uint8_t *)w.nupd, w.group);
+    hipLaunchKernelGGL(k_group_scan, dim3(1), dim3(kScanThreads), 0, d->stream, ngroups, w.group, w.total);
+    if (hash_groups)
+        hipLaunchKernelGGL(k_flags_hash, dim3((uint32_t)hash_groups), dim3(kGroupTiles), 0, d->stream,
+                           (const uint8_t *)d->d_flags, w.maps);
+    HIP_TRY(hipGetLastError());
+    std::vector<uint64_t> back(8 + hash_groups * sizeof(FnvMap) / 8);
+    HIP_TRY(copy_sync(d->stream, back.data(), w.total, back.size() * 8, hipMemcpyDeviceToHost));
+    d->ntiles = back[0];
+    d->nwall = back[1];
+    d->n_inl = (uint32_t)back[2];
+    d->n_inlrec = back[3];
+    d->n_updated = back[4];
+    d->flags_hash = fnv_finish((const FnvMap *)(back.data() + 8), hash_groups, flags + hash_groups * kGroupCells,
+                               d->ncells - hash_groups * kGroupCells);
+    const uint64_t size[5] = {d->ntiles * sizeof(TileRec), d->nwall * 256, d->nwall * 256, d->n_inlrec * kRecWords * 4,
+                              (uint64_t)d->n_inl * Q * 64 * sizeof(float)};
+    uint64_t at[6] = {0};
+    for (int j = 0; j < 5; ++j) {
+        at[j + 1] = at[j] + (size[j] + 255) / 256 * 256;
+        d->device_bytes += size[j];
+    }
+    if (dalloc(d->stream, (void **)&d->d_tables, at[5]) != hipSuccess)
+        return fail(LBM_ERR_OOM, "domain tables");
+    d->d_tiles = (TileRec *)d->d_tables;
+    d->d_wall = (uint32_t *)(d->d_tables + at[1]);
+    d->d_inlet = (uint32_t *)(d->d_tables + at[2]);
+    d->d_inlrec = (uint32_t *)(d->d_tables + at[3]);
+    d->d_iterm = (float *)(d->d_tables + at[4]);
+    hipLaunchKernelGGL(k_tile_write, tiles, dim3(256), 0, d->stream, k, nt, (const uint64_t *)w.tile,
+                       (const uint32_t *)w.group, d->outlets ? 1u : 0u, (const uint32_t *)w.inlet_cells,
+                       (uint32_t)n_inlet, d->d_tiles, d->d_wall, d->d_inlet, d->d_inlrec);
+    HIP_TRY(hipGetLastError());
+    return LBM_OK;
+}
+
+// Host copies of the tile list and, per lane of the wall tiles, the link
+// masks and the inlet links.
+int host_tables(const lbm_domain *d, std::vector<TileRec> &tiles, std::vector<uint32_t> &wall,
+                std::vector<uint32_t> &inlm)
+{
+    tiles.resize(d->ntiles);
+    wall.resize(d->nwall * 64);
+    inlm.resize(d->nwall * 64);
+    std::vector<uint32_t> rec(d->n_inlrec * kRecWords);
+    HIP_TRY(copy_sync(d->stream, tiles.data(), d->d_tiles, tiles.size() * sizeof(TileRec), hipMemcpyDeviceToHost));
+    HIP_TRY(copy_sync(d->stream, wall.data(), d->d_wall, wall.size() * 4, hipMemcpyDeviceToHost));
+    HIP_TRY(copy_sync(d->stream, inlm.data(), d->d_inlet, inlm.size() * 4, hipMemcpyDeviceToHost));
+    HIP_TRY(copy_sync(d->stream, rec.data(), d->d_inlrec, rec.size() * 4, hipMemcpyDeviceToHost));
+    for (uint32_t &v : inlm)
+        v = v == kNoRec ? 0u : rec[(size_t)v * kRecWords];
+    return LBM_OK;
+}
+
 int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int storage, void *hip_stream, void *fa,
            lbm_domain **out)
 {
@@ -749,21 +673,8 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         return fail(LBM_ERR_ARG, "domain of %llu cells; the limit is 2^32 - 64 cells", (unsigned long long)ncells);
     std::vector<uint64_t> inlet_cells;
     bool outlets = false;
-    uint64_t hash = 0xcbf29ce484222325ull;
-    for (uint64_t c = 0; c < ncells; ++c) {
-        const uint8_t f = flags[c];
-        if (f > LBM_OUTLET)
-            return fail(LBM_ERR_ARG, "bad flag %u at cell %llu", f, (unsigned long long)c);
-        if (f == LBM_OUTLET && ((c % nx) != (uint64_t)nx - 1 || (periodic & 1u)))
-            return fail(LBM_ERR_ARG, "outlet cell %llu not on the last x plane of a non-periodic x axis",
-                        (unsigned long long)c);
-        if (f == LBM_INLET)
-            inlet_cells.push_back(c);
-        outlets |= f == LBM_OUTLET;
-        hash = (hash ^ f) * 0x100000001b3ull;
-    }
-    Tiles T;
-    build_tiles(flags, nx, ny, nz, periodic, inlet_cells, outlets, T);
+    if (int rc = check_flags(flags, nx, ncells, periodic, inlet_cells, outlets))
+        return rc;
 
     lbm_domain *d = new lbm_domain();
     d->nx = nx;
@@ -775,17 +686,6 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     d->P = P;
     d->bytes = bufbytes;
     d->outlets = outlets;
-    d->flags_hash = hash;
-    d->ntiles = T.recs.size();
-    d->nwall = T.wall.size() / 64;
-    d->n_updated = T.n_updated;
-    d->h_tiles = T.recs;
-    d->h_wall = T.wall;
-    d->h_inlm.assign(T.wall.size(), 0u);
-    for (size_t l = 0; l < T.inlet.size(); ++l)
-        if (T.inlet[l] != kNoRec)
-            d->h_inlm[l] = T.inlrec[(size_t)T.inlet[l] * kRecWords];
-    d->n_inl = T.n_inl;
     d->inlet_cells = std::move(inlet_cells);
     auto bail = [&](int code) {
         free_domain(d);
@@ -807,6 +707,9 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         d->device_bytes += n;
         return true;
     };
+    auto up = [&](void *dst, const void *src, size_t n) {
+        return copy_sync(d->stream, dst, src, n, hipMemcpyHostToDevice) == hipSuccess;
+    };
     if (fa) {
         d->own_buffers = false;
         d->buf = (char *)fa;
@@ -816,18 +719,12 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     } else if (!dmalloc((void **)&d->buf, bufbytes)) {
         return bail(fail(LBM_ERR_OOM, "population array (%llu bytes)", (unsigned long long)bufbytes));
     }
-    if (!dmalloc((void **)&d->d_flags, ncells) || !dmalloc((void **)&d->d_tiles, T.recs.size() * sizeof(TileRec)) ||
-        !dmalloc((void **)&d->d_wall, T.wall.size() * 4) || !dmalloc((void **)&d->d_inlet, T.inlet.size() * 4) ||
-        !dmalloc((void **)&d->d_inlrec, T.inlrec.size() * 4) || status_alloc(d->status) != hipSuccess ||
-        !dmalloc((void **)&d->d_iterm, (size_t)T.n_inl * Q * 64 * sizeof(float)))
+    if (!dmalloc((void **)&d->d_flags, ncells) || status_alloc(d->status) != hipSuccess)
         return bail(fail(LBM_ERR_OOM, "domain tables"));
-    auto up = [&](void *dst, const void *src, size_t n) {
-        return copy_sync(d->stream, dst, src, n, hipMemcpyHostToDevice) == hipSuccess;
-    };
-    if (!up(d->d_flags, flags, ncells) || !up(d->d_tiles, T.recs.data(), T.recs.size() * sizeof(TileRec)) ||
-        !up(d->d_wall, T.wall.data(), T.wall.size() * 4) || !up(d->d_inlet, T.inlet.data(), T.inlet.size() * 4) ||
-        !up(d->d_inlrec, T.inlrec.data(), T.inlrec.size() * 4))
-        return bail(fail(LBM_ERR_DEVICE, "upload of domain tables failed"));
+    if (!up(d->d_flags, flags, ncells))
+        return bail(fail(LBM_ERR_DEVICE, "upload of the flags failed"));
+    if (int rc = build_tables(d, flags))
+        return bail(rc);
     if (build_inlet_terms(d) != hipSuccess)
         return bail(fail(LBM_ERR_DEVICE, "inlet terms"));
     d->omega = d->omega_b = 1.0 / 0.6;
@@ -1026,12 +923,16 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
     const size_t nco = (size_t)d->nwall * Q * 64;
+    std::vector<TileRec> tiles;
+    std::vector<uint32_t> wall, inlm;
+    if (int rc = host_tables(d, tiles, wall, inlm))
+        return rc;
     std::vector<float2> coef;
-    std::vector<uint32_t> bz(d->h_tiles.size(), 0u);
+    std::vector<uint32_t> bz(tiles.size(), 0u);
     if (q) {
         coef.assign(nco, make_float2(1.f, 0.f));
-        for (size_t t = 0; t < d->h_tiles.size(); ++t) {
-            const TileRec &r = d->h_tiles[t];
+        for (size_t t = 0; t < tiles.size(); ++t) {
+            const TileRec &r = tiles[t];
             if (r.wall < 0)
                 continue;
             for (uint32_t l = 0; l < 64; ++l) {
@@ -1039,7 +940,7 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
                     continue;
                 const uint64_t c = (uint64_t)r.tile * 64 + l;
                 const size_t wl = (size_t)r.wall * 64 + l;
-                const uint32_t m = d->h_wall[wl], il = d->h_inlm[wl];
+                const uint32_t m = wall[wl], il = inlm[wl];
                 for (int k = 0; k < Q; ++k) {
                     if (!((m >> k) & 1u) || ((il >> k) & 1u))
                         continue; // not a wall link
@@ -1085,10 +986,8 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
         d->device_bytes -= nco * (sizeof(float2) + sizeof(float));
     }
     for (size_t t = 0; t < bz.size(); ++t)
-        d->h_tiles[t].bz = bz[t];
-    if (!d->h_tiles.empty())
-        HIP_TRY(copy_sync(d->stream, d->d_tiles, d->h_tiles.data(), d->h_tiles.size() * sizeof(TileRec),
-                          hipMemcpyHostToDevice));
+        tiles[t].bz = bz[t];
+    HIP_TRY(copy_sync(d->stream, d->d_tiles, tiles.data(), tiles.size() * sizeof(TileRec), hipMemcpyHostToDevice));
     if (any) {
         HIP_TRY(copy_sync(d->stream, d->d_bzc, coef.data(), nco * sizeof(float2), hipMemcpyHostToDevice));
         // kept values of lanes and links without a curved coefficient are
