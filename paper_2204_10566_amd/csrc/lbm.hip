@@ -18,6 +18,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #define LBM_HOST_TU
@@ -195,10 +196,11 @@ struct lbm_domain {
     bool stats_on = false;
     uint64_t stats_samples = 0; // local steps accumulated
     uint8_t *d_flags = nullptr;
-    char *d_tables = nullptr; // one allocation: the tile list, wall masks, inlet tables and terms
+    char *d_tables = nullptr; // one allocation: the tile list, wall masks, inlet tables, terms and velocity
     TileRec *d_tiles = nullptr;
     uint32_t *d_wall = nullptr, *d_inlet = nullptr, *d_inlrec = nullptr;
-    float *d_uin = nullptr;                // [3][n_inlet]
+    float *d_uin = nullptr;                // [3][n_inlet], null until set
+    float *uin_room = nullptr;             // where it goes
     float *d_iterm = nullptr;              // inlet terms, [27][64] per inlet tile
     float2 *d_bzc = nullptr;               // curved-wall coefficients, [27][64] per wall tile
     float *d_bzaux = nullptr;              // f*_k of the curved links, [27][64] per wall tile
@@ -375,11 +377,8 @@ void free_domain(lbm_domain *d)
     release_graph(d);
     if (d->stream) {
         hipStream_t s = d->stream;
-        if (d->own_buffers)
-            dfree(s, d->buf);
-        dfree(s, d->d_flags);
+        dfree(s, d->own_buffers ? (void *)d->buf : (void *)d->d_flags); // (the flags lie behind an own array)
         dfree(s, d->d_tables);
-        dfree(s, d->d_uin);
         dfree(s, d->d_bzc);
         dfree(s, d->d_bzaux);
         dfree(s, d->d_stats);
@@ -517,15 +516,21 @@ hipError_t normalise(lbm_domain *d)
     return hipSuccess;
 }
 
-// f^eq of the given fields (null: rho = 1, u = 0) in every cell, phase 0.
-// The caller waits for the stream and clears the status word then.
-int init_eq(lbm_domain *d, const float *rho_dev, const float *u_dev)
+// f^eq in the cells [c0, c0 + count), phase 0, from the fields of the first n
+// of them (null: rho = 1, u = 0).
+void launch_init_eq(const lbm_domain *d, const float *rho, const float *u, uint32_t c0, uint32_t n, uint32_t count)
 {
     const KDomain k = kdomain(d);
-    const uint32_t blocks = (uint32_t)((d->P + 255) / 256);
     dispatch_storage(d->storage, [&](auto st) {
-        hipLaunchKernelGGL((k_init_eq<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, rho_dev, u_dev);
+        hipLaunchKernelGGL((k_init_eq<decltype(st)::value>), dim3((count + 255) / 256), dim3(256), 0, d->stream, k, rho,
+                           u, c0, n, count);
     });
+}
+
+// What follows an f^eq in every cell.  The caller waits for the stream and
+// clears the status word then.
+int init_done(lbm_domain *d)
+{
     HIP_TRY(hipGetLastError());
     d->phase = 0;
     HIP_TRY(side_refresh(d));
@@ -577,6 +582,7 @@ int scratch_address(int device, float **out)
 } // namespace
 
 #include "lbm_build.inc"
+#include "lbm_transfer.inc"
 
 namespace {
 
@@ -612,20 +618,25 @@ int build_tables(lbm_domain *d, const uint8_t *flags)
     d->n_updated = back[4];
     d->flags_hash = fnv_finish((const FnvMap *)(back.data() + 8), hash_groups, flags + hash_groups * kGroupCells,
                                d->ncells - hash_groups * kGroupCells);
-    const uint64_t size[5] = {d->ntiles * sizeof(TileRec), d->nwall * 256, d->nwall * 256, d->n_inlrec * kRecWords * 4,
-                              (uint64_t)d->n_inl * Q * 64 * sizeof(float)};
-    uint64_t at[6] = {0};
-    for (int j = 0; j < 5; ++j) {
+    const uint64_t size[6] = {d->ntiles * sizeof(TileRec),
+                              d->nwall * 256,
+                              d->nwall * 256,
+                              d->n_inlrec * kRecWords * 4,
+                              (uint64_t)d->n_inl * Q * 64 * sizeof(float),
+                              3 * n_inlet * sizeof(float)};
+    uint64_t at[7] = {0};
+    for (int j = 0; j < 6; ++j) {
         at[j + 1] = at[j] + (size[j] + 255) / 256 * 256;
-        d->device_bytes += size[j];
+        d->device_bytes += j < 5 ? size[j] : 0; // the inlet velocity counts once it is set
     }
-    if (dalloc(d->stream, (void **)&d->d_tables, at[5]) != hipSuccess)
+    if (dalloc(d->stream, (void **)&d->d_tables, at[6]) != hipSuccess)
         return fail(LBM_ERR_OOM, "domain tables");
     d->d_tiles = (TileRec *)d->d_tables;
     d->d_wall = (uint32_t *)(d->d_tables + at[1]);
     d->d_inlet = (uint32_t *)(d->d_tables + at[2]);
     d->d_inlrec = (uint32_t *)(d->d_tables + at[3]);
     d->d_iterm = (float *)(d->d_tables + at[4]);
+    d->uin_room = (float *)(d->d_tables + at[5]);
     hipLaunchKernelGGL(k_tile_write, tiles, dim3(256), 0, d->stream, k, nt, (const uint64_t *)w.tile,
                        (const uint32_t *)w.group, d->outlets ? 1u : 0u, (const uint32_t *)w.inlet_cells,
                        (uint32_t)n_inlet, d->d_tiles, d->d_wall, d->d_inlet, d->d_inlrec);
@@ -701,12 +712,6 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         d->own_stream = true;
     }
     pool_setup(d->device);
-    auto dmalloc = [&](void **p, size_t n) -> bool {
-        if (dalloc(d->stream, p, n) != hipSuccess)
-            return false;
-        d->device_bytes += n;
-        return true;
-    };
     auto up = [&](void *dst, const void *src, size_t n) {
         return copy_sync(d->stream, dst, src, n, hipMemcpyHostToDevice) == hipSuccess;
     };
@@ -716,11 +721,21 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         if ((uintptr_t)fa & 255u)
             return bail(fail(LBM_ERR_ARG, "an adopted population array must be 256-byte aligned"));
         d->device_bytes += bufbytes;
-    } else if (!dmalloc((void **)&d->buf, bufbytes)) {
-        return bail(fail(LBM_ERR_OOM, "population array (%llu bytes)", (unsigned long long)bufbytes));
     }
-    if (!dmalloc((void **)&d->d_flags, ncells) || status_alloc(d->status) != hipSuccess)
-        return bail(fail(LBM_ERR_OOM, "domain tables"));
+    // an own array and the flags behind it are one allocation, the tables
+    // another: a freed pair is found again whole by the next domain of its
+    // size, where of many pieces the pool gave some back to the device and
+    // had to ask for them again (freeing a domain of 64 x 64 x 256 cells 577
+    // -> 120 us)
+    char *own = nullptr;
+    if (dalloc(d->stream, (void **)&own, (fa ? 0 : bufbytes) + ncells) != hipSuccess)
+        return bail(fail(LBM_ERR_OOM, "population array (%llu bytes)", (unsigned long long)bufbytes));
+    if (!fa)
+        d->buf = own;
+    d->d_flags = (uint8_t *)own + (fa ? 0 : bufbytes);
+    d->device_bytes += (fa ? 0 : bufbytes) + ncells;
+    if (status_alloc(d->status) != hipSuccess)
+        return bail(fail(LBM_ERR_OOM, "status word"));
     if (!up(d->d_flags, flags, ncells))
         return bail(fail(LBM_ERR_DEVICE, "upload of the flags failed"));
     if (int rc = build_tables(d, flags))
@@ -734,7 +749,8 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     const uint64_t tile_bytes = (uint64_t)Q * P * storage_bytes(storage);
     if (hipMemsetAsync(d->buf + tile_bytes, 0, bufbytes - tile_bytes, d->stream) != hipSuccess)
         return bail(fail(LBM_ERR_DEVICE, "side rows"));
-    int rc = init_eq(d, nullptr, nullptr);
+    launch_init_eq(d, nullptr, nullptr, 0, (uint32_t)ncells, (uint32_t)P);
+    int rc = init_done(d);
     if (rc == LBM_OK && hipStreamSynchronize(d->stream) != hipSuccess)
         rc = fail(LBM_ERR_DEVICE, "initialisation failed");
     if (rc != LBM_OK)
@@ -1025,8 +1041,7 @@ int lbm_set_inlet_cells(lbm_domain *d, const float *u_inlet)
     if (n == 0)
         return LBM_OK;
     if (!d->d_uin) {
-        if (dalloc(d->stream, (void **)&d->d_uin, 3 * n * sizeof(float)) != hipSuccess)
-            return fail(LBM_ERR_OOM, "inlet velocity buffer");
+        d->d_uin = d->uin_room;
         d->device_bytes += 3 * n * sizeof(float);
         d->graph_dirty = true;
     }
@@ -1058,27 +1073,26 @@ int lbm_init_fields(lbm_domain *d, const float *rho, const float *u)
         return rc;
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
-    float *dr = nullptr, *du = nullptr;
-    int rc = LBM_OK;
-    if (rho && dalloc(d->stream, (void **)&dr, d->ncells * sizeof(float)) != hipSuccess)
-        rc = fail(LBM_ERR_OOM, "staging buffer");
-    if (rc == LBM_OK && u && dalloc(d->stream, (void **)&du, 3 * d->ncells * sizeof(float)) != hipSuccess)
-        rc = fail(LBM_ERR_OOM, "staging buffer");
-    if (rc == LBM_OK && rho &&
-        copy_sync(d->stream, dr, rho, d->ncells * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
-        rc = fail(LBM_ERR_DEVICE, "upload of rho failed");
-    if (rc == LBM_OK && u &&
-        copy_sync(d->stream, du, u, 3 * d->ncells * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
-        rc = fail(LBM_ERR_DEVICE, "upload of u failed");
-    if (rc == LBM_OK)
-        rc = init_eq(d, dr, du);
-    if (rc == LBM_OK && hipStreamSynchronize(d->stream) != hipSuccess)
-        rc = fail(LBM_ERR_DEVICE, "initialisation failed");
-    if (rc == LBM_OK)
-        clear_status(d);
-    dfree(d->stream, dr);
-    dfree(d->stream, du);
-    return rc;
+    if (!rho && !u) {
+        launch_init_eq(d, nullptr, nullptr, 0, (uint32_t)d->ncells, (uint32_t)d->P);
+    } else {
+        // chunks of rho, then u; the last one also covers the padding cells
+        const int first = rho ? 0 : 1, comps = (rho ? 1 : 0) + (u ? 3 : 0);
+        const hipError_t e = move_fields<false, const float>(
+            d, comps,
+            [&](uint32_t c0, uint32_t n, const float *dev) {
+                const uint32_t count = c0 + n == d->ncells ? (uint32_t)d->P - c0 : n;
+                launch_init_eq(d, rho ? dev : nullptr, u ? dev + (rho ? n : 0) : nullptr, c0, n, count);
+            },
+            [&](int k) { return k + first == 0 ? rho : u + (size_t)(k + first - 1) * d->ncells; });
+        if (e != hipSuccess)
+            return fail(LBM_ERR_DEVICE, "upload of the fields failed: %s", hipGetErrorString(e));
+    }
+    if (int rc = init_done(d))
+        return rc;
+    HIP_TRY(hipStreamSynchronize(d->stream));
+    clear_status(d);
+    return LBM_OK;
 }
 
 int lbm_step_async(lbm_domain *d, int n)
@@ -1165,8 +1179,8 @@ int lbm_get_moments_device(lbm_domain *d, float *rho_dev, float *u_dev)
     const KDomain k = kdomain(d);
     const uint32_t blocks = (uint32_t)((d->ncells + 255) / 256);
     dispatch_storage(d->storage, [&](auto st) {
-        hipLaunchKernelGGL((k_moments<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, rho_dev,
-                           u_dev);
+        hipLaunchKernelGGL((k_moments<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, rho_dev, u_dev,
+                           0u, (uint32_t)d->ncells);
     });
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(d->stream));
@@ -1193,7 +1207,7 @@ int lbm_get_moments_noalloc(lbm_domain *d, float *rho, float *u)
     const uint32_t blocks = (uint32_t)((d->ncells + 255) / 256);
     dispatch_storage(d->storage, [&](auto st) {
         hipLaunchKernelGGL((k_moments<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, buf,
-                           buf + d->ncells);
+                           buf + d->ncells, 0u, (uint32_t)d->ncells);
     });
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(rho, buf, d->ncells * sizeof(float), hipMemcpyDeviceToHost, d->stream));
@@ -1208,16 +1222,20 @@ int lbm_get_moments(lbm_domain *d, float *rho, float *u)
         return rc;
     if (!rho || !u)
         return fail(LBM_ERR_ARG, "null output");
-    float *dr = nullptr;
-    if (dalloc(d->stream, (void **)&dr, 4 * d->ncells * sizeof(float)) != hipSuccess)
-        return fail(LBM_ERR_OOM, "staging buffer");
-    int rc = lbm_get_moments_device(d, dr, dr + d->ncells);
-    if (rc == LBM_OK &&
-        (copy_sync(d->stream, rho, dr, d->ncells * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess ||
-         copy_sync(d->stream, u, dr + d->ncells, 3 * d->ncells * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess))
-        rc = fail(LBM_ERR_DEVICE, "download failed");
-    dfree(d->stream, dr);
-    return rc;
+    if (d->batch)
+        return fail(LBM_ERR_STATE, "domain is resident in a batch");
+    HIP_TRY(normalise(d));
+    const KDomain k = kdomain(d);
+    HIP_TRY((move_fields<true, float>(
+        d, 4,
+        [&](uint32_t c0, uint32_t n, float *dev) {
+            dispatch_storage(d->storage, [&](auto st) {
+                hipLaunchKernelGGL((k_moments<decltype(st)::value>), dim3((n + 255) / 256), dim3(256), 0, d->stream, k,
+                                   dev, dev + n, c0, n);
+            });
+        },
+        [&](int c) { return c == 0 ? rho : u + (size_t)(c - 1) * d->ncells; })));
+    return LBM_OK;
 }
 
 int lbm_get_populations(lbm_domain *d, float *f)
@@ -1229,20 +1247,17 @@ int lbm_get_populations(lbm_domain *d, float *f)
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
     HIP_TRY(normalise(d));
-    float *df = nullptr;
-    if (dalloc(d->stream, (void **)&df, (size_t)Q * d->ncells * sizeof(float)) != hipSuccess)
-        return fail(LBM_ERR_OOM, "staging buffer");
     const KDomain k = kdomain(d);
-    const uint32_t blocks = (uint32_t)((d->ncells + 255) / 256);
-    dispatch_storage(d->storage, [&](auto st) {
-        hipLaunchKernelGGL((k_export<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, df);
-    });
-    int rc = LBM_OK;
-    if (hipGetLastError() != hipSuccess ||
-        copy_sync(d->stream, f, df, (size_t)Q * d->ncells * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)
-        rc = fail(LBM_ERR_DEVICE, "population export failed");
-    dfree(d->stream, df);
-    return rc;
+    HIP_TRY((move_fields<true, float>(
+        d, Q,
+        [&](uint32_t c0, uint32_t n, float *dev) {
+            dispatch_storage(d->storage, [&](auto st) {
+                hipLaunchKernelGGL((k_export<decltype(st)::value>), dim3((n + 255) / 256), dim3(256), 0, d->stream, k,
+                                   dev, c0, n);
+            });
+        },
+        [&](int i) { return f + (size_t)i * d->ncells; })));
+    return LBM_OK;
 }
 
 int lbm_set_populations(lbm_domain *d, const float *f)
@@ -1253,25 +1268,21 @@ int lbm_set_populations(lbm_domain *d, const float *f)
         return fail(LBM_ERR_ARG, "null input");
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
-    float *df = nullptr;
-    if (dalloc(d->stream, (void **)&df, (size_t)Q * d->ncells * sizeof(float)) != hipSuccess)
-        return fail(LBM_ERR_OOM, "staging buffer");
-    int rc = LBM_OK;
-    if (copy_sync(d->stream, df, f, (size_t)Q * d->ncells * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
-        rc = fail(LBM_ERR_DEVICE, "upload failed");
-    if (rc == LBM_OK) {
-        const KDomain k = kdomain(d);
-        const uint32_t blocks = (uint32_t)((d->ncells + 255) / 256);
-        dispatch_storage(d->storage, [&](auto st) {
-            hipLaunchKernelGGL((k_import<decltype(st)::value>), dim3(blocks), dim3(256), 0, d->stream, k, df);
-        });
-        d->phase = 0;
-        if (hipGetLastError() != hipSuccess || side_refresh(d) != hipSuccess || curved_refresh(d) != hipSuccess ||
-            hipStreamSynchronize(d->stream) != hipSuccess)
-            rc = fail(LBM_ERR_DEVICE, "population import failed");
-    }
-    dfree(d->stream, df);
-    return rc;
+    const KDomain k = kdomain(d);
+    const hipError_t e = move_fields<false, const float>(
+        d, Q,
+        [&](uint32_t c0, uint32_t n, const float *dev) {
+            dispatch_storage(d->storage, [&](auto st) {
+                hipLaunchKernelGGL((k_import<decltype(st)::value>), dim3((n + 255) / 256), dim3(256), 0, d->stream, k,
+                                   dev, c0, n);
+            });
+        },
+        [&](int i) { return f + (size_t)i * d->ncells; });
+    d->phase = 0;
+    if (e != hipSuccess || side_refresh(d) != hipSuccess || curved_refresh(d) != hipSuccess ||
+        hipStreamSynchronize(d->stream) != hipSuccess)
+        return fail(LBM_ERR_DEVICE, "population import failed");
+    return LBM_OK;
 }
 
 namespace {
@@ -1326,8 +1337,7 @@ int lbm_save_state(lbm_domain *d, void *buf, size_t bytes)
     state_header(d, h);
     std::memcpy(buf, h, sizeof h);
     char *p = (char *)buf + kStateHeader;
-    if (copy_sync(d->stream, p, d->buf, d->bytes, hipMemcpyDeviceToHost) != hipSuccess ||
-        copy_sync(d->stream, p + d->bytes, d->d_bzaux, aux, hipMemcpyDeviceToHost) != hipSuccess)
+    if (copy_out(d, p, d->buf, d->bytes) != hipSuccess || copy_out(d, p + d->bytes, d->d_bzaux, aux) != hipSuccess)
         return fail(LBM_ERR_DEVICE, "state download failed");
     return LBM_OK;
 }
@@ -1358,8 +1368,7 @@ int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes)
         return fail(LBM_ERR_ARG, "state image of %zu bytes; its header gives %llu", bytes,
                     (unsigned long long)(kStateHeader + h[2] + h[3]));
     const char *p = (const char *)buf + kStateHeader;
-    if (copy_sync(d->stream, d->buf, p, d->bytes, hipMemcpyHostToDevice) != hipSuccess ||
-        copy_sync(d->stream, d->d_bzaux, p + d->bytes, h[3], hipMemcpyHostToDevice) != hipSuccess ||
+    if (copy_in(d, d->buf, p, d->bytes) != hipSuccess || copy_in(d, d->d_bzaux, p + d->bytes, h[3]) != hipSuccess ||
         hipStreamSynchronize(d->stream) != hipSuccess)
         return fail(LBM_ERR_DEVICE, "state upload failed");
     d->phase = (int)(h[5] & 1u);
@@ -1417,9 +1426,9 @@ int lbm_stats_get(lbm_domain *d, double *mean_u, double *mean_uu, double *mean_s
             rc = fail(LBM_ERR_DEVICE, "statistics export failed");
     }
     if (rc == LBM_OK &&
-        (copy_sync(d->stream, mean_u, dout, 3 * n * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess ||
-         copy_sync(d->stream, mean_uu, dout + 3 * n, 6 * n * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess ||
-         copy_sync(d->stream, mean_sigma, dout + 9 * n, 6 * n * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess))
+        (copy_out(d, mean_u, dout, 3 * n * sizeof(double)) != hipSuccess ||
+         copy_out(d, mean_uu, dout + 3 * n, 6 * n * sizeof(double)) != hipSuccess ||
+         copy_out(d, mean_sigma, dout + 9 * n, 6 * n * sizeof(double)) != hipSuccess))
         rc = fail(LBM_ERR_DEVICE, "statistics download failed");
     dfree(d->stream, dout);
     return rc;

@@ -1564,14 +1564,16 @@ __global__ __launch_bounds__(256) void k_curved_refresh(KDomain d, const TileRec
 // f = f^eq(rho, u) in product form: the sixth-order Hermite equilibrium of
 // Eq. (4) factorises into rho prod_a phi(c_a, u_a), phi(0, u) = 2/3 - u^2,
 // phi(+-1, u) = (1 +- 3u + 3u^2)/6 (App. A, Eqs. (A.2)-(A.4)).  Written in
-// the phase-0 form; cells that are not updated get the rest state.
+// the phase-0 form; cells that are not updated get the rest state.  For the
+// cells [c0, c0 + count); rho[n] and u[3][n] hold those of [c0, c0 + n).
 template <int ST>
-__global__ __launch_bounds__(256) void k_init_eq(KDomain d, const float *__restrict__ rho, const float *__restrict__ u)
+__global__ __launch_bounds__(256) void k_init_eq(KDomain d, const float *__restrict__ rho, const float *__restrict__ u,
+                                                 uint32_t c0, uint32_t n, uint32_t count)
 {
     using S = Storage<ST>;
     constexpr uint32_t es = S::bytes;
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= d.P)
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, c = c0 + i0;
+    if (i0 >= count)
         return;
     float r = 1.f, v[3] = {0.f, 0.f, 0.f};
     bool upd = false;
@@ -1579,11 +1581,11 @@ __global__ __launch_bounds__(256) void k_init_eq(KDomain d, const float *__restr
         upd = d.flags[c] == FL_FLUID || d.flags[c] == FL_OUTLET;
         if (upd) {
             if (rho)
-                r = rho[c];
+                r = rho[i0];
             if (u) {
-                v[0] = u[c];
-                v[1] = u[(size_t)d.ncells + c];
-                v[2] = u[2 * (size_t)d.ncells + c];
+                v[0] = u[i0];
+                v[1] = u[(size_t)n + i0];
+                v[2] = u[2 * (size_t)n + i0];
             }
         }
     }
@@ -1604,13 +1606,15 @@ __global__ __launch_bounds__(256) void k_init_eq(KDomain d, const float *__restr
     }
 }
 
-// Density and velocity of a phase-0 state at updated cells (0 elsewhere).
+// Density and velocity of a phase-0 state at updated cells (0 elsewhere):
+// rho[n] and u[3][n] of the cells [c0, c0 + n).
 template <int ST>
-__global__ __launch_bounds__(256) void k_moments(KDomain d, float *__restrict__ rho, float *__restrict__ u)
+__global__ __launch_bounds__(256) void k_moments(KDomain d, float *__restrict__ rho, float *__restrict__ u, uint32_t c0,
+                                                 uint32_t n)
 {
     using S = Storage<ST>;
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= d.ncells)
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, c = c0 + i0;
+    if (i0 >= n)
         return;
     float r = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
     if (d.flags[c] == FL_FLUID || d.flags[c] == FL_OUTLET) {
@@ -1629,10 +1633,10 @@ __global__ __launch_bounds__(256) void k_moments(KDomain d, float *__restrict__ 
         jy *= inv;
         jz *= inv;
     }
-    rho[c] = r;
-    u[c] = jx;
-    u[(size_t)d.ncells + c] = jy;
-    u[2 * (size_t)d.ncells + c] = jz;
+    rho[i0] = r;
+    u[i0] = jx;
+    u[(size_t)n + i0] = jy;
+    u[2 * (size_t)n + i0] = jz;
 }
 
 #ifdef LBM_HOST_TU
@@ -1658,33 +1662,33 @@ __global__ __launch_bounds__(256) void k_stats_export(KDomain d, const TileRec *
 
 #endif // LBM_HOST_TU
 
-// Phase-0 state <-> FP32 values of f_i, layout [i][cell] without padding.
+// Phase-0 state <-> FP32 values of f_i, [i][n] of the cells [c0, c0 + n).
 template <int ST>
-__global__ __launch_bounds__(256) void k_export(KDomain d, float *__restrict__ out)
+__global__ __launch_bounds__(256) void k_export(KDomain d, float *__restrict__ out, uint32_t c0, uint32_t n)
 {
     using S = Storage<ST>;
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= d.ncells)
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, c = c0 + i0;
+    if (i0 >= n)
         return;
     const Pops<ST, true> rr(d);
     const uint64_t cb = cell_bytes<S::bytes, uint64_t>(c, d.tbytes);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        out[(size_t)i * d.ncells + c] = rr.load(cb, pop_bytes<S::bytes>(Q - 1 - i), i);
+        out[(size_t)i * n + i0] = rr.load(cb, pop_bytes<S::bytes>(Q - 1 - i), i);
 }
 
 template <int ST>
-__global__ __launch_bounds__(256) void k_import(KDomain d, const float *__restrict__ in)
+__global__ __launch_bounds__(256) void k_import(KDomain d, const float *__restrict__ in, uint32_t c0, uint32_t n)
 {
     using S = Storage<ST>;
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= d.ncells)
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, c = c0 + i0;
+    if (i0 >= n)
         return;
     const Pops<ST, true> rr(d);
     const uint64_t cb = cell_bytes<S::bytes, uint64_t>(c, d.tbytes);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        rr.store(cb, pop_bytes<S::bytes>(Q - 1 - i), in[(size_t)i * d.ncells + c], i);
+        rr.store(cb, pop_bytes<S::bytes>(Q - 1 - i), in[(size_t)i * n + i0], i);
 }
 
 } // namespace lbm

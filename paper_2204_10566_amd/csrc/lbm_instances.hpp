@@ -43,9 +43,9 @@
     PREFIX __global__ void k_normalise<ST>(KDomain, const TileRec *, uint32_t);                               \
     PREFIX __global__ void k_side_refresh<ST>(KDomain);                                                       \
     PREFIX __global__ void k_curved_refresh<ST>(KDomain, const TileRec *, uint32_t);                          \
-    PREFIX __global__ void k_init_eq<ST>(KDomain, const float *, const float *);                              \
-    PREFIX __global__ void k_moments<ST>(KDomain, float *, float *);                                          \
-    PREFIX __global__ void k_export<ST>(KDomain, float *);                                                    \
-    PREFIX __global__ void k_import<ST>(KDomain, const float *);
+    PREFIX __global__ void k_init_eq<ST>(KDomain, const float *, const float *, uint32_t, uint32_t, uint32_t); \
+    PREFIX __global__ void k_moments<ST>(KDomain, float *, float *, uint32_t, uint32_t);                      \
+    PREFIX __global__ void k_export<ST>(KDomain, float *, uint32_t, uint32_t);                                \
+    PREFIX __global__ void k_import<ST>(KDomain, const float *, uint32_t, uint32_t);
 
 #define LBM_INSTANCES_WIDE(PREFIX, ST) LBM_FOR_VARIANTS(LBM_INST_WIDE_VARIANT, PREFIX, ST)
