@@ -196,11 +196,12 @@ struct lbm_domain {
     bool stats_on = false;
     uint64_t stats_samples = 0; // local steps accumulated
     uint8_t *d_flags = nullptr;
-    char *d_tables = nullptr; // one allocation: the tile list, wall masks, inlet tables, terms and velocity
+    char *d_tables = nullptr; // one allocation: the tile list, wall masks, inlet tables, terms and velocity, outlet targets
     TileRec *d_tiles = nullptr;
     uint32_t *d_wall = nullptr, *d_inlet = nullptr, *d_inlrec = nullptr;
     float *d_uin = nullptr;                // [3][n_inlet], null until set
     float *uin_room = nullptr;             // where it goes
+    uint16_t *d_targets = nullptr;         // outlet cells fed by each last-plane cell, [nz][ny]
     float *d_iterm = nullptr;              // inlet terms, [27][64] per inlet tile
     float2 *d_bzc = nullptr;               // curved-wall coefficients, [27][64] per wall tile
     float *d_bzaux = nullptr;              // f*_k of the curved links, [27][64] per wall tile
@@ -296,6 +297,7 @@ KDomain kdomain(const lbm_domain *d)
     k.stats = d->stats_on ? d->d_stats : nullptr;
     k.sstride = (uint32_t)(d->ntiles * 64);
     k.wall = d->d_wall;
+    k.targets = d->d_targets;
     k.iterm = d->d_iterm;
     k.bzc = d->d_bzc;
     k.bzaux = d->d_bzaux;
@@ -618,18 +620,19 @@ int build_tables(lbm_domain *d, const uint8_t *flags)
     d->n_updated = back[4];
     d->flags_hash = fnv_finish((const FnvMap *)(back.data() + 8), hash_groups, flags + hash_groups * kGroupCells,
                                d->ncells - hash_groups * kGroupCells);
-    const uint64_t size[6] = {d->ntiles * sizeof(TileRec),
+    const uint64_t size[7] = {d->ntiles * sizeof(TileRec),
                               d->nwall * 256,
                               d->nwall * 256,
                               d->n_inlrec * kRecWords * 4,
                               (uint64_t)d->n_inl * Q * 64 * sizeof(float),
-                              3 * n_inlet * sizeof(float)};
-    uint64_t at[7] = {0};
-    for (int j = 0; j < 6; ++j) {
+                              3 * n_inlet * sizeof(float),
+                              d->outlets ? (uint64_t)d->ny * d->nz * sizeof(uint16_t) : 0};
+    uint64_t at[8] = {0};
+    for (int j = 0; j < 7; ++j) {
         at[j + 1] = at[j] + (size[j] + 255) / 256 * 256;
-        d->device_bytes += j < 5 ? size[j] : 0; // the inlet velocity counts once it is set
+        d->device_bytes += j != 5 ? size[j] : 0; // the inlet velocity counts once it is set
     }
-    if (dalloc(d->stream, (void **)&d->d_tables, at[6]) != hipSuccess)
+    if (dalloc(d->stream, (void **)&d->d_tables, at[7]) != hipSuccess)
         return fail(LBM_ERR_OOM, "domain tables");
     d->d_tiles = (TileRec *)d->d_tables;
     d->d_wall = (uint32_t *)(d->d_tables + at[1]);
@@ -637,6 +640,10 @@ int build_tables(lbm_domain *d, const uint8_t *flags)
     d->d_inlrec = (uint32_t *)(d->d_tables + at[3]);
     d->d_iterm = (float *)(d->d_tables + at[4]);
     d->uin_room = (float *)(d->d_tables + at[5]);
+    d->d_targets = (uint16_t *)(d->d_tables + at[6]);
+    if (d->outlets)
+        hipLaunchKernelGGL(k_outlet_targets, dim3((uint32_t)(((uint64_t)d->ny * d->nz + 255) / 256)), dim3(256), 0,
+                           d->stream, k, d->d_targets);
     hipLaunchKernelGGL(k_tile_write, tiles, dim3(256), 0, d->stream, k, nt, (const uint64_t *)w.tile,
                        (const uint32_t *)w.group, d->outlets ? 1u : 0u, (const uint32_t *)w.inlet_cells,
                        (uint32_t)n_inlet, d->d_tiles, d->d_wall, d->d_inlet, d->d_inlrec);
