@@ -203,7 +203,7 @@ struct lbm_domain {
     float *uin_room = nullptr;             // where it goes
     uint16_t *d_targets = nullptr;         // outlet cells fed by each last-plane cell, [nz][ny]
     float *d_iterm = nullptr;              // inlet terms, [27][64] per inlet tile
-    float2 *d_bzc = nullptr;               // curved-wall coefficients, [27][64] per wall tile
+    float *d_bzc = nullptr;                // curved-wall coefficients, [27][64] per wall tile
     float *d_bzaux = nullptr;              // f*_k of the curved links, [27][64] per wall tile
     uint64_t n_inlrec = 0;                 // inlet records
     uint32_t n_inl = 0;                    // inlet tiles
@@ -950,10 +950,10 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
     std::vector<uint32_t> wall, inlm;
     if (int rc = host_tables(d, tiles, wall, inlm))
         return rc;
-    std::vector<float2> coef;
-    std::vector<uint32_t> bz(tiles.size(), 0u);
+    std::vector<float> coef;
+    std::vector<uint32_t> bz(tiles.size(), 0u), bzf(tiles.size(), 0u);
     if (q) {
-        coef.assign(nco, make_float2(1.f, 0.f));
+        coef.assign(nco, 1.f);
         for (size_t t = 0; t < tiles.size(); ++t) {
             const TileRec &r = tiles[t];
             if (r.wall < 0)
@@ -971,17 +971,12 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
                     if (!(qq > 0.0 && qq <= 1.0))
                         return fail(LBM_ERR_ARG, "wall fraction %g of link %d of cell %llu outside (0, 1]", qq, k,
                                     (unsigned long long)c);
-                    double a, b;
                     if (qq == 0.5 || (qq < 0.5 && ((m >> (Q - 1 - k)) & 1u)))
                         continue; // halfway rule
-                    if (qq < 0.5) {
-                        a = 2.0 * qq;
-                        b = 1.0 - 2.0 * qq;
-                    } else {
-                        a = 1.0 / (2.0 * qq);
-                        b = -(1.0 - 1.0 / (2.0 * qq));
-                    }
-                    coef[((size_t)r.wall * Q + k) * 64 + l] = make_float2((float)a, (float)b);
+                    const bool near = qq < 0.5;
+                    const float a = (float)(near ? 2.0 * qq : 1.0 / (2.0 * qq));
+                    coef[((size_t)r.wall * Q + k) * 64 + l] = near ? a : -a;
+                    bzf[t] |= near ? 0u : 1u << k;
                     bz[t] |= 1u << k;
                 }
             }
@@ -992,27 +987,29 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
         any |= b != 0;
     HIP_TRY(normalise(d));
     if (any && !d->d_bzc) {
-        if (dalloc(d->stream, (void **)&d->d_bzc, nco * sizeof(float2)) != hipSuccess ||
+        if (dalloc(d->stream, (void **)&d->d_bzc, nco * sizeof(float)) != hipSuccess ||
             dalloc(d->stream, (void **)&d->d_bzaux, nco * sizeof(float)) != hipSuccess) {
             dfree(d->stream, d->d_bzc);
             d->d_bzc = nullptr;
             d->d_bzaux = nullptr;
             return fail(LBM_ERR_OOM, "curved-wall tables");
         }
-        d->device_bytes += nco * (sizeof(float2) + sizeof(float));
+        d->device_bytes += nco * 2 * sizeof(float);
     }
     if (!any && d->d_bzc) {
         dfree(d->stream, d->d_bzc);
         dfree(d->stream, d->d_bzaux);
         d->d_bzc = nullptr;
         d->d_bzaux = nullptr;
-        d->device_bytes -= nco * (sizeof(float2) + sizeof(float));
+        d->device_bytes -= nco * 2 * sizeof(float);
     }
-    for (size_t t = 0; t < bz.size(); ++t)
+    for (size_t t = 0; t < bz.size(); ++t) {
         tiles[t].bz = bz[t];
+        tiles[t].bzf = bzf[t];
+    }
     HIP_TRY(copy_sync(d->stream, d->d_tiles, tiles.data(), tiles.size() * sizeof(TileRec), hipMemcpyHostToDevice));
     if (any) {
-        HIP_TRY(copy_sync(d->stream, d->d_bzc, coef.data(), nco * sizeof(float2), hipMemcpyHostToDevice));
+        HIP_TRY(copy_sync(d->stream, d->d_bzc, coef.data(), nco * sizeof(float), hipMemcpyHostToDevice));
         // kept values of lanes and links without a curved coefficient are
         // never written: zero, so that state images are deterministic
         HIP_TRY(hipMemsetAsync(d->d_bzaux, 0, nco * sizeof(float), d->stream));

@@ -128,14 +128,14 @@ struct KDomain {
     uint32_t outlet;         // 0: zero-gradient outlet, 1: constant pressure rho_out / 3 (kernel variant kVarPressure)
     uint32_t high1;          // every rate of order >= 3 is one (see collide_lane)
     float rho_out;
-    const float2 *bzc;       // curved-wall coefficients, [27][64] per wall tile (see curved_walls)
+    const float *bzc;        // curved-wall coefficients, [27][64] per wall tile (see curved_walls)
     float *bzaux;            // f*_k of the lanes' previous step, [27][64] per wall tile
     uint32_t rowtiles;       // nx / 64 when nx is a multiple of 64 (stream_tile_rows), else 0
     FastDiv drow;            // division by rowtiles
     uint32_t feq_order;      // 2..5: explicit equilibrium truncated at that order (variant kVarFeq); 6: full
 };
 
-// One entry of a tile list (40 bytes; a wave reads it with scalar loads).
+// One entry of a tile list (44 bytes; a wave reads it with scalar loads).
 // An interior tile needs nothing else; a wall tile adds one 32-bit link
 // mask per lane (KDomain::wall).
 struct TileRec {
@@ -148,8 +148,9 @@ struct TileRec {
     uint32_t edge;   // 1: an updated cell of the tile lies on the outlet plane x = nx - 1
     uint32_t ord;    // position of the tile in its domain's tile list
     uint32_t bz;     // links with a curved-wall coefficient in some cell of the tile
+    uint32_t bzf;    // of these, links at a wall fraction > 1/2 in some cell
 };
-static_assert(sizeof(TileRec) == 40, "tile record layout");
+static_assert(sizeof(TileRec) == 44, "tile record layout");
 
 // Tile-major population layout: the 27 populations of the 64 cells of a
 // tile are one contiguous block, population i of the cell in lane l at
@@ -903,34 +904,53 @@ __device__ __forceinline__ void outlet_ghost_shift(const KDomain &d, float rho, 
 // the value pulled for kbar, which is f*_kbar(x + c_k) (the host gives the
 // halfway coefficients where kbar is no plain link).  f*_k(x) cannot be
 // read from the slots: in the streaming step the lane of x + c_k owns
-// that slot, so each step keeps it in bzaux.  The host stores per lane
-// and link (a, b): f_k <- a f_k + b f_kbar for b > 0, a f_k - b aux_k
-// otherwise; (1, 0) where the lane has no curved link k.
+// that slot, so each step keeps it in bzaux.  Both rules are f_k <- a f_k +
+// (1 - a) o, with o = f_kbar and a = 2q, or o = aux_k and a = 1/(2q); the
+// host stores per lane and link +a for the first, -a for the second (a = 1
+// where the lane has no curved link k).  A near link's f_kbar is a plain
+// pull, which no rule changes, so f is updated in place.
+//
+// The coefficients and kept values of nine links at a time are loaded before
+// any is used: loading each where it is used was two dependent loads per
+// link, ten links a tile, the longest chain of the step.  One coefficient
+// instead of the pair (a, b), and kept values only of links some lane of the
+// tile has at q > 1/2, move 34 instead of 61 MB a step on the 52 x 52 x 1043
+// nozzle (beside 356 MB of populations).  Its streaming step went 107 -> 88
+// us and its local step 78 -> 60 us (167 -> 151 us with statistics).
 __device__ __forceinline__ void curved_walls(const KDomain &d, const TileRec &rec, uint32_t lane, float (&f)[Q])
 {
     const size_t base = (size_t)(uint32_t)rec.wall * (Q * 64u) + lane;
-    float nf[Q];
 #pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        if ((rec.bz >> k) & 1u) {
-            const float2 c = d.bzc[base + k * 64u];
-            const float other = c.y > 0.f ? f[Q - 1 - k] : d.bzaux[base + k * 64u];
-            nf[k] = c.x * f[k] + __builtin_fabsf(c.y) * other;
+    for (int z = 0; z < Q; z += 9) {
+        float a[9], x[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int k = z + j;
+            a[j] = 1.f;
+            x[j] = 0.f;
+            if ((rec.bz >> k) & 1u)
+                a[j] = d.bzc[base + k * 64u];
+            if ((rec.bzf >> k) & 1u)
+                x[j] = d.bzaux[base + k * 64u];
+        }
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int k = z + j;
+            if ((rec.bz >> k) & 1u) {
+                const float m = __builtin_fabsf(a[j]);
+                f[k] = __builtin_fmaf(m, f[k], (1.f - m) * (a[j] > 0.f ? f[Q - 1 - k] : x[j]));
+            }
         }
     }
-#pragma unroll
-    for (int k = 0; k < Q; ++k)
-        if ((rec.bz >> k) & 1u)
-            f[k] = nf[k];
 }
 
-// Keeps f*_k of the lane's curved links for the next step.
+// Keeps f*_k of the lane's curved links at q > 1/2 for the next step.
 __device__ __forceinline__ void curved_keep(const KDomain &d, const TileRec &rec, uint32_t lane, const float (&f)[Q])
 {
     const size_t base = (size_t)(uint32_t)rec.wall * (Q * 64u) + lane;
 #pragma unroll
     for (int k = 0; k < Q; ++k)
-        if ((rec.bz >> k) & 1u)
+        if ((rec.bzf >> k) & 1u)
             d.bzaux[base + k * 64u] = f[k];
 }
 
@@ -1579,14 +1599,14 @@ __global__ __launch_bounds__(256) void k_curved_refresh(KDomain d, const TileRec
     if (t >= ntiles)
         return;
     const TileRec rec = tiles[t];
-    if (rec.wall < 0 || !rec.bz || !lane_active(rec, lane))
+    if (rec.wall < 0 || !rec.bzf || !lane_active(rec, lane))
         return;
     const Pops<ST, true> r(d);
     const uint64_t self = cell_bytes<es, uint64_t>(rec.tile * 64u + lane, d.tbytes);
     float f[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k)
-        f[k] = ((rec.bz >> k) & 1u) ? r.load(self, pop_bytes<es>(Q - 1 - k), k) : 0.f;
+        f[k] = ((rec.bzf >> k) & 1u) ? r.load(self, pop_bytes<es>(Q - 1 - k), k) : 0.f;
     curved_keep(d, rec, lane, f);
 }
 
