@@ -184,6 +184,7 @@ struct lbm_domain {
     uint64_t ncells = 0, P = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    bool in_ring = false; // counted among the users of its device's pinned chunks
     bool own_buffers = true;
     int device = 0;
     char *buf = nullptr;  // the population array
@@ -374,6 +375,8 @@ void release_graph(lbm_domain *d)
     d->graph_dirty = true;
 }
 
+void ring_leave(int device);
+
 void free_domain(lbm_domain *d)
 {
     release_graph(d);
@@ -388,6 +391,8 @@ void free_domain(lbm_domain *d)
             (void)hipStreamDestroy(s);
     }
     status_free(d->status);
+    if (d->in_ring)
+        ring_leave(d->device);
     delete d;
 }
 
@@ -711,6 +716,7 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     };
     if (hipGetDevice(&d->device) != hipSuccess)
         return bail(fail(LBM_ERR_DEVICE, "no HIP device"));
+    d->in_ring = ring_join(d->device);
     if (hip_stream) {
         d->stream = (hipStream_t)hip_stream;
     } else {
