@@ -105,11 +105,12 @@ uint64_t array_bytes(uint64_t P, int ny, int nz, int storage)
     return (Q * P * es + 18ull * ny * nz * es + 255) / 256 * 256;
 }
 
-// Status words of domains: 4 bytes each of pinned host memory that the step
-// kernels write, so that waiting for steps is one stream synchronisation
-// and a host read, with no copy behind it (one step of a 16^3 box, waited
-// for: 34.8 -> 14.5 us).  The words come from blocks of 1024; a block is
-// given back when none of its words is in use and another block is left.
+// Status words of domains: 4 bytes each of pinned host memory that the first
+// unstable waves write (check_state), so that waiting for steps is one stream
+// synchronisation and a host read, with no copy behind it (one step of a 16^3
+// box, waited for: 34.8 -> 14.5 us).  The words come from blocks of 1024; a
+// block is given back when none of its words is in use and another block is
+// left.
 struct StatusWord {
     uint32_t *host = nullptr, *dev = nullptr;
 };
@@ -209,7 +210,8 @@ struct lbm_domain {
     uint64_t n_inlrec = 0;                 // inlet records
     uint32_t n_inl = 0;                    // inlet tiles
     std::vector<uint64_t> inlet_cells;     // inlet cells, ascending (index = inlet ordinal)
-    StatusWord status;                     // set by a step that goes unstable
+    StatusWord status;                     // set by a step that goes unstable, and ...
+    StatusTwin *d_status = nullptr;        // ... its twin in device memory, in front of the flags
     uint64_t ntiles = 0, nwall = 0, n_updated = 0;
     double omega = 1.0, omega_b = 1.0;
     double omega_o[4] = {1.0, 1.0, 1.0, 1.0}; // orders 3..6
@@ -304,7 +306,7 @@ KDomain kdomain(const lbm_domain *d)
     k.bzaux = d->d_bzaux;
     k.rowtiles = d->nx % 64 == 0 ? (uint32_t)(d->nx / 64) : 0u;
     k.drow = make_fastdiv(k.rowtiles ? k.rowtiles : 1u);
-    k.status = d->status.dev;
+    k.status = &d->d_status->word;
     k.P = (uint32_t)d->P;
     k.tbytes = (uint32_t)(Q * 64 * storage_bytes(d->storage));
     k.side = d->P / 64 * k.tbytes;
@@ -382,7 +384,8 @@ void free_domain(lbm_domain *d)
     release_graph(d);
     if (d->stream) {
         hipStream_t s = d->stream;
-        dfree(s, d->own_buffers ? (void *)d->buf : (void *)d->d_flags); // (the flags lie behind an own array)
+        // (the status word and the flags lie behind an own array)
+        dfree(s, d->own_buffers ? (void *)d->buf : (void *)d->d_status);
         dfree(s, d->d_tables);
         dfree(s, d->d_bzc);
         dfree(s, d->d_bzaux);
@@ -545,11 +548,17 @@ int init_done(lbm_domain *d)
     return LBM_OK;
 }
 
-// A new state (no step in flight): stable until a step says otherwise.
-void clear_status(lbm_domain *d)
+// A new state (no step in flight): stable until a step says otherwise.  The
+// device word is set exactly when the host word is.
+int clear_status(lbm_domain *d)
 {
-    *d->status.host = 0;
+    if (status_set(d->status)) {
+        HIP_TRY(hipMemsetAsync(&d->d_status->word, 0, sizeof(uint32_t), d->stream));
+        HIP_TRY(hipStreamSynchronize(d->stream));
+        *d->status.host = 0;
+    }
     d->unstable = false;
+    return LBM_OK;
 }
 
 // Cells rounded up to whole 64-cell tiles.
@@ -611,7 +620,8 @@ int build_tables(lbm_domain *d, const uint8_t *flags)
     hipLaunchKernelGGL(k_tile_count, tiles, dim3(256), 0, d->stream, k, nt, w.tile, w.nupd);
     hipLaunchKernelGGL(k_group_count, dim3(ngroups), dim3(kGroupTiles), 0, d->stream, nt, (const uint64_t *)w.tile,
                        (const uint8_t *)w.nupd, w.group);
-    hipLaunchKernelGGL(k_group_scan, dim3(1), dim3(kScanThreads), 0, d->stream, ngroups, w.group, w.total);
+    hipLaunchKernelGGL(k_group_scan, dim3(1), dim3(kScanThreads), 0, d->stream, ngroups, w.group, w.total,
+                       d->d_status, d->status.dev);
     if (hash_groups)
         hipLaunchKernelGGL(k_flags_hash, dim3((uint32_t)hash_groups), dim3(kGroupTiles), 0, d->stream,
                            (const uint8_t *)d->d_flags, w.maps);
@@ -735,18 +745,21 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
             return bail(fail(LBM_ERR_ARG, "an adopted population array must be 256-byte aligned"));
         d->device_bytes += bufbytes;
     }
-    // an own array and the flags behind it are one allocation, the tables
-    // another: a freed pair is found again whole by the next domain of its
-    // size, where of many pieces the pool gave some back to the device and
-    // had to ask for them again (freeing a domain of 64 x 64 x 256 cells 577
-    // -> 120 us)
+    // an own array with the status word and the flags behind it is one
+    // allocation, the tables another: a freed pair is found again whole by
+    // the next domain of its size, where of many pieces the pool gave some
+    // back to the device and had to ask for them again (freeing a domain of
+    // 64 x 64 x 256 cells 577 -> 120 us)
+    constexpr size_t kStatusRoom = 256; // keeps the flags aligned
+    const size_t before = fa ? 0 : bufbytes;
     char *own = nullptr;
-    if (dalloc(d->stream, (void **)&own, (fa ? 0 : bufbytes) + ncells) != hipSuccess)
+    if (dalloc(d->stream, (void **)&own, before + kStatusRoom + ncells) != hipSuccess)
         return bail(fail(LBM_ERR_OOM, "population array (%llu bytes)", (unsigned long long)bufbytes));
     if (!fa)
         d->buf = own;
-    d->d_flags = (uint8_t *)own + (fa ? 0 : bufbytes);
-    d->device_bytes += (fa ? 0 : bufbytes) + ncells;
+    d->d_status = (StatusTwin *)(own + before);
+    d->d_flags = (uint8_t *)own + before + kStatusRoom;
+    d->device_bytes += before + kStatusRoom + ncells;
     if (status_alloc(d->status) != hipSuccess)
         return bail(fail(LBM_ERR_OOM, "status word"));
     if (!up(d->d_flags, flags, ncells))
@@ -768,7 +781,6 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
         rc = fail(LBM_ERR_DEVICE, "initialisation failed");
     if (rc != LBM_OK)
         return bail(rc);
-    clear_status(d);
     *out = d;
     return LBM_OK;
 }
@@ -1101,8 +1113,7 @@ int lbm_init_fields(lbm_domain *d, const float *rho, const float *u)
     if (int rc = init_done(d))
         return rc;
     HIP_TRY(hipStreamSynchronize(d->stream));
-    clear_status(d);
-    return LBM_OK;
+    return clear_status(d);
 }
 
 int lbm_step_async(lbm_domain *d, int n)
@@ -1382,7 +1393,8 @@ int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes)
         hipStreamSynchronize(d->stream) != hipSuccess)
         return fail(LBM_ERR_DEVICE, "state upload failed");
     d->phase = (int)(h[5] & 1u);
-    clear_status(d);
+    if (int rc = clear_status(d))
+        return rc;
     d->unstable = (h[5] >> 1) != 0;
     return LBM_OK;
 }

@@ -103,6 +103,15 @@ __host__ __device__ inline uint32_t fdiv(uint32_t n, FastDiv f)
     return (t + ((n - t) >> f.s1)) >> f.s2;
 }
 
+// Status of a stand-alone domain: the device word, and the pinned host word
+// that is set along with it (a batch copies its own status words to the host).
+// The address lies behind the word, not in KDomain, where the step kernels
+// would load it with their other arguments and spill scalar registers for it.
+struct StatusTwin {
+    uint32_t word, pad;
+    uint32_t *report;
+};
+
 // Everything a kernel needs to update one domain.
 struct KDomain {
     char *buf;               // the population array: P / 64 tile blocks, then the outlet side rows
@@ -110,7 +119,7 @@ struct KDomain {
     const uint32_t *wall;    // link masks of wall tiles, 64 per wall tile
     const uint16_t *targets; // per last-plane cell (y, z): the outlet cells it feeds (outlet_target)
     const float *iterm;      // inlet terms, [27][64] per inlet tile
-    uint32_t *status;        // 1: a step went unstable (pinned host memory, or a batch's device table)
+    uint32_t *status;        // device memory, 1: a step went unstable (a stand-alone domain's: StatusTwin::word)
     uint64_t side;           // byte offset of the side rows: 2 x 9 rows of ny * nz elements
     uint32_t P;              // cells rounded up to whole tiles
     uint32_t tbytes;         // bytes of one tile block: 27 x 64 populations
@@ -724,15 +733,15 @@ __device__ __forceinline__ float collide_feq(float (&f)[Q], float omega, float o
 
 // Collision of a lane in kernel variant V.  In a packed launch a step runs
 // one variant for every domain, the general collision as soon as one domain
-// needs it (DYN); a domain whose higher-order rates are all one then still
+// needs it (PACKED); a domain whose higher-order rates are all one then still
 // takes the reduced form, chosen per domain (the branch is wave-uniform), so
 // that it ends bit for bit where it ends alone.
-template <int V, bool DYN>
+template <int V, bool PACKED>
 __device__ __forceinline__ float collide_lane(const KDomain &d, float (&f)[Q], float &ux, float &uy, float &uz,
                                               float (&m2)[6])
 {
     if constexpr ((V & kVarFeq) != 0) {
-        if constexpr (DYN) {
+        if constexpr (PACKED) {
             // a packed domain with the full equilibrium takes its own path
             if (d.feq_order >= 6u) {
                 if (d.high1)
@@ -743,7 +752,7 @@ __device__ __forceinline__ float collide_lane(const KDomain &d, float (&f)[Q], f
         return collide_feq(f, d.omega, d.omega_b, d.omega_o, d.feq_order, ux, uy, uz, m2);
     } else if constexpr ((V & kVarH1) != 0) {
         return collide<true>(f, d.omega, d.omega_b, d.omega_o, ux, uy, uz, m2);
-    } else if constexpr (DYN) {
+    } else if constexpr (PACKED) {
         if (d.high1)
             return collide<true>(f, d.omega, d.omega_b, d.omega_o, ux, uy, uz, m2);
         return collide<false>(f, d.omega, d.omega_b, d.omega_o, ux, uy, uz, m2);
@@ -860,10 +869,29 @@ __device__ __forceinline__ bool outlet_target(const KDomain &d, uint32_t y, uint
     return oy && oz;
 }
 
+// An unstable state spreads over its domain and the remaining steps are
+// taken all the same, so every wave may come here in every step: it reads the
+// device word, and only the waves that find it clear set it and the host word.
+// 1000 steps of a 96 x 96 x 768 FP16S nozzle with one NaN take 24.7 ms (24.4
+// when stable), against 1320 ms with a write over PCIe by every unstable wave
+// and 174 ms with an atomic on the device word.  (Plain stores: an atomic
+// exchange would let one wave through, and cost the large kernels of the
+// explicit equilibrium 3 % by its length.  The host word's address space is
+// named, since a store through a generic pointer makes every later load of
+// the tile loop wait for all others.)  A packed launch has its status words in
+// device memory alone, and evicts an unstable domain.
+template <bool PACKED>
 __device__ __forceinline__ void check_state(const KDomain &d, float rho, float ux, float uy, float uz)
 {
-    if (!(rho > 0.f) || !(__builtin_fabsf(ux) + __builtin_fabsf(uy) + __builtin_fabsf(uz) < 1e30f))
-        __hip_atomic_store(d.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (!(rho > 0.f) || !(__builtin_fabsf(ux) + __builtin_fabsf(uy) + __builtin_fabsf(uz) < 1e30f)) {
+        if constexpr (PACKED)
+            __hip_atomic_store(d.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        else if (__hip_atomic_load(d.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+            __hip_atomic_store(d.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store((__attribute__((address_space(1))) uint32_t *)((const StatusTwin *)d.status)->report, 1u,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
 
 // Inlet term of link k of the lane (0 where link k is not an inlet link).
@@ -975,7 +1003,7 @@ __device__ __forceinline__ Off slot_of(const KDomain &d, const Coords &C, int k,
 
 // Phase 0 -> 1.  EDGE: the tile has cells on the outlet plane (tile entry
 // `edge`); the other tiles compile without the outlet handling.
-template <int ST, int V, bool EDGE, bool DYN = false, bool W64 = false>
+template <int ST, int V, bool EDGE, bool PACKED = false, bool W64 = false>
 __device__ __forceinline__ void stream_tile_t(const KDomain &d, const TileRec &rec, uint32_t lane)
 {
     using S = Storage<ST>;
@@ -1035,8 +1063,8 @@ __device__ __forceinline__ void stream_tile_t(const KDomain &d, const TileRec &r
 
     prio_compute();
     float ux, uy, uz, m2[6];
-    const float rho = collide_lane<V, DYN>(d, f, ux, uy, uz, m2);
-    check_state(d, rho, ux, uy, uz);
+    const float rho = collide_lane<V, PACKED>(d, f, ux, uy, uz, m2);
+    check_state<PACKED>(d, rho, ux, uy, uz);
     if constexpr ((V & kVarCurved) != 0) {
         if (wall && rec.bz)
             curved_keep(d, rec, lane, f);
@@ -1145,7 +1173,7 @@ __device__ __forceinline__ RowAddr<Off> row_addr(const KDomain &d, const TileRec
 
 // Phase 0 -> 1 for a tile of a row-aligned domain: stream_tile_t with the
 // addressing above.  EDGE: the tile holds a cell of the outlet plane.
-template <int ST, int V, bool EDGE, bool DYN = false, bool W64 = false>
+template <int ST, int V, bool EDGE, bool PACKED = false, bool W64 = false>
 __device__ __forceinline__ void stream_tile_rows(const KDomain &d, const TileRec &rec, uint32_t lane)
 {
     using S = Storage<ST>;
@@ -1195,8 +1223,8 @@ __device__ __forceinline__ void stream_tile_rows(const KDomain &d, const TileRec
 
     prio_compute();
     float ux, uy, uz, m2[6];
-    const float rho = collide_lane<V, DYN>(d, f, ux, uy, uz, m2);
-    check_state(d, rho, ux, uy, uz);
+    const float rho = collide_lane<V, PACKED>(d, f, ux, uy, uz, m2);
+    check_state<PACKED>(d, rho, ux, uy, uz);
     if constexpr ((V & kVarCurved) != 0) {
         if (wall && rec.bz)
             curved_keep(d, rec, lane, f);
@@ -1283,7 +1311,7 @@ __device__ __forceinline__ void local_load(const KDomain &d, const TileRec &rec,
 // exactly in FP64 from the FP32 velocities, so that averages over long
 // windows keep their digits and the Reynolds stress <u_a u_b> - <u_a><u_b>
 // does not cancel away.
-template <int ST, int V, bool DYN = false, bool W64 = false>
+template <int ST, int V, bool PACKED = false, bool W64 = false>
 __device__ __forceinline__ void local_finish(const KDomain &d, const TileRec &rec, uint32_t lane, float (&f)[Q])
 {
     using P = Pops<ST, W64>;
@@ -1300,8 +1328,8 @@ __device__ __forceinline__ void local_finish(const KDomain &d, const TileRec &re
     }
     prio_compute();
     float ux, uy, uz, m2[6];
-    const float rho = collide_lane<V, DYN>(d, f, ux, uy, uz, m2);
-    check_state(d, rho, ux, uy, uz);
+    const float rho = collide_lane<V, PACKED>(d, f, ux, uy, uz, m2);
+    check_state<PACKED>(d, rho, ux, uy, uz);
     if constexpr ((V & kVarCurved) != 0) {
         if (rec.wall >= 0 && rec.bz)
             curved_keep(d, rec, lane, f);
@@ -1336,12 +1364,12 @@ __device__ __forceinline__ void local_finish(const KDomain &d, const TileRec &re
     }
 }
 
-template <int ST, int V, bool DYN = false, bool W64 = false>
+template <int ST, int V, bool PACKED = false, bool W64 = false>
 __device__ __forceinline__ void local_tile(const KDomain &d, const TileRec &rec, uint32_t lane)
 {
     float f[Q];
     local_load<ST, W64>(d, rec, lane, f);
-    local_finish<ST, V, DYN, W64>(d, rec, lane, f);
+    local_finish<ST, V, PACKED, W64>(d, rec, lane, f);
 }
 
 #ifdef LBM_HOST_TU
@@ -1458,7 +1486,6 @@ __global__ __launch_bounds__(kBlock, (kBatchedMinBlocks<V, PHASE>)) void k_colli
     const KDomain *__restrict__ doms, const TileRec *__restrict__ tiles, uint32_t ntiles,
     const uint32_t *__restrict__ ctrl, uint32_t soff)
 {
-    constexpr bool DYN = (V & kVarH1) == 0;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t g = ctrl[1] + soff;
     const uint32_t nw = gridDim.x * kWavesPerBlock;
@@ -1473,17 +1500,17 @@ __global__ __launch_bounds__(kBlock, (kBatchedMinBlocks<V, PHASE>)) void k_colli
         if constexpr (PHASE == 0u) {
             if constexpr (ROWS) {
                 if (rec.edge)
-                    stream_tile_rows<ST, V, true, DYN>(dd, rec, lane);
+                    stream_tile_rows<ST, V, true, true>(dd, rec, lane);
                 else
-                    stream_tile_rows<ST, V, false, DYN>(dd, rec, lane);
+                    stream_tile_rows<ST, V, false, true>(dd, rec, lane);
             } else {
                 if (rec.edge)
-                    stream_tile_t<ST, V, true, DYN>(dd, rec, lane);
+                    stream_tile_t<ST, V, true, true>(dd, rec, lane);
                 else
-                    stream_tile_t<ST, V, false, DYN>(dd, rec, lane);
+                    stream_tile_t<ST, V, false, true>(dd, rec, lane);
             }
         } else {
-            local_tile<ST, V, DYN>(dd, rec, lane);
+            local_tile<ST, V, true>(dd, rec, lane);
         }
     }
 }
