@@ -248,7 +248,10 @@ int lbm_set_inlet_cells(lbm_domain *d, const float *u_inlet);
  * every updated cell.
  *   rho  host, ncells floats, or NULL for 1.
  *   u    host, 3*ncells floats [component][cell], or NULL for 0.
- * Clears a sticky LBM_ERR_UNSTABLE.
+ * Clears a sticky LBM_ERR_UNSTABLE.  Errors: LBM_ERR_OOM (no pinned memory
+ * for the transfer; nothing changed), LBM_ERR_DEVICE (the state may be
+ * replaced in part: the domain is LBM_ERR_UNSTABLE until a call succeeds),
+ * LBM_ERR_STATE for a domain resident in a batch.
  */
 int lbm_init_fields(lbm_domain *d, const float *rho, const float *u);
 
@@ -322,7 +325,10 @@ int lbm_get_moments_device(lbm_domain *d, float *rho_dev, float *u_dev);
 int lbm_get_populations(lbm_domain *d, float *f);
 
 /* Overwrite the stored populations (FP32 values of f_i, [i][cell], host);
- * converted to the domain's storage. */
+ * converted to the domain's storage.  Errors: LBM_ERR_OOM (nothing changed),
+ * LBM_ERR_DEVICE (the state may be replaced in part: the domain is
+ * LBM_ERR_UNSTABLE until lbm_init_fields), LBM_ERR_STATE for a domain
+ * resident in a batch. */
 int lbm_set_populations(lbm_domain *d, const float *f);
 
 /*
@@ -368,7 +374,9 @@ int lbm_save_state(lbm_domain *d, void *buf, size_t bytes);
  * and flags, and must have curved walls exactly when the saved one had;
  * otherwise LBM_ERR_ARG (a different size, tag or grid) or LBM_ERR_STATE
  * (other flags, curved walls on one side only, domain resident in a
- * batch), and the domain is unchanged.  LBM_ERR_DEVICE on a failed copy. */
+ * batch), and the domain is unchanged.  LBM_ERR_OOM or LBM_ERR_DEVICE on a
+ * failed copy; if it had begun, the domain is LBM_ERR_UNSTABLE until
+ * lbm_init_fields or lbm_load_state succeeds. */
 int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes);
 
 /*
@@ -487,10 +495,11 @@ int lbm_batch_destroy(lbm_batch *b);
  * (no device call).  Returns LBM_OK or LBM_ERR_STATE with a message. */
 int lbm_selftest_host(void);
 
-/* Test hook for the error paths of batch admission: the n-th (n >= 1)
- * table allocation or staged upload made by the batch calls from now on
- * fails as if device memory were exhausted; n = 0 disables.  Returns
- * LBM_ERR_ARG for n < 0. */
+/* Test hook for error paths: the n-th (n >= 1) table allocation or staged
+ * upload made by the batch calls, or pinned buffer or chunk taken by a
+ * transfer of fields, from now on fails as if memory were exhausted (a chunk:
+ * as if the device refused it); n = 0 disables.  Returns LBM_ERR_ARG for
+ * n < 0. */
 int lbm_debug_fail_after(int n);
 
 /* *wide = 1 if the domain's step kernels address its array with 64-bit

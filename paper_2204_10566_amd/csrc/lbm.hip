@@ -597,6 +597,24 @@ int scratch_address(int device, float **out)
 
 } // namespace
 
+namespace {
+
+// Test hook (lbm_debug_fail_after): the n-th fallible allocation or upload
+// of the batch calls, pinned pair or chunk of a field transfer from now on
+// fails as if memory were exhausted.
+std::atomic<int> g_fail_countdown{0};
+
+bool injected_failure()
+{
+    int c = g_fail_countdown.load();
+    while (c > 0)
+        if (g_fail_countdown.compare_exchange_weak(c, c - 1))
+            return c == 1;
+    return false;
+}
+
+} // namespace
+
 #include "lbm_build.inc"
 #include "lbm_transfer.inc"
 
@@ -1100,16 +1118,17 @@ int lbm_init_fields(lbm_domain *d, const float *rho, const float *u)
     } else {
         // chunks of rho, then u; the last one also covers the padding cells
         const int first = rho ? 0 : 1, comps = (rho ? 1 : 0) + (u ? 3 : 0);
-        const hipError_t e = move_fields<false, const float>(
+        const Moved m = move_fields<false, const float>(
             d, comps,
             [&](uint32_t c0, uint32_t n, const float *dev) {
                 const uint32_t count = c0 + n == d->ncells ? (uint32_t)d->P - c0 : n;
                 launch_init_eq(d, rho ? dev : nullptr, u ? dev + (rho ? n : 0) : nullptr, c0, n, count);
             },
             [&](int k) { return k + first == 0 ? rho : u + (size_t)(k + first - 1) * d->ncells; });
-        if (e != hipSuccess)
-            return fail(LBM_ERR_DEVICE, "upload of the fields failed: %s", hipGetErrorString(e));
+        if (int rc = moved_in(d, m, "upload of the fields"))
+            return rc;
     }
+    d->unstable = true; // until the new state is complete
     if (int rc = init_done(d))
         return rc;
     HIP_TRY(hipStreamSynchronize(d->stream));
@@ -1247,7 +1266,7 @@ int lbm_get_moments(lbm_domain *d, float *rho, float *u)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
     HIP_TRY(normalise(d));
     const KDomain k = kdomain(d);
-    HIP_TRY((move_fields<true, float>(
+    const Moved m = move_fields<true, float>(
         d, 4,
         [&](uint32_t c0, uint32_t n, float *dev) {
             dispatch_storage(d->storage, [&](auto st) {
@@ -1255,8 +1274,8 @@ int lbm_get_moments(lbm_domain *d, float *rho, float *u)
                                    dev, dev + n, c0, n);
             });
         },
-        [&](int c) { return c == 0 ? rho : u + (size_t)(c - 1) * d->ncells; })));
-    return LBM_OK;
+        [&](int c) { return c == 0 ? rho : u + (size_t)(c - 1) * d->ncells; });
+    return moved_out(m, "moments");
 }
 
 int lbm_get_populations(lbm_domain *d, float *f)
@@ -1269,7 +1288,7 @@ int lbm_get_populations(lbm_domain *d, float *f)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
     HIP_TRY(normalise(d));
     const KDomain k = kdomain(d);
-    HIP_TRY((move_fields<true, float>(
+    const Moved m = move_fields<true, float>(
         d, Q,
         [&](uint32_t c0, uint32_t n, float *dev) {
             dispatch_storage(d->storage, [&](auto st) {
@@ -1277,8 +1296,8 @@ int lbm_get_populations(lbm_domain *d, float *f)
                                    dev, c0, n);
             });
         },
-        [&](int i) { return f + (size_t)i * d->ncells; })));
-    return LBM_OK;
+        [&](int i) { return f + (size_t)i * d->ncells; });
+    return moved_out(m, "population export");
 }
 
 int lbm_set_populations(lbm_domain *d, const float *f)
@@ -1290,7 +1309,7 @@ int lbm_set_populations(lbm_domain *d, const float *f)
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
     const KDomain k = kdomain(d);
-    const hipError_t e = move_fields<false, const float>(
+    const Moved m = move_fields<false, const float>(
         d, Q,
         [&](uint32_t c0, uint32_t n, const float *dev) {
             dispatch_storage(d->storage, [&](auto st) {
@@ -1299,10 +1318,14 @@ int lbm_set_populations(lbm_domain *d, const float *f)
             });
         },
         [&](int i) { return f + (size_t)i * d->ncells; });
+    if (int rc = moved_in(d, m, "population import"))
+        return rc;
     d->phase = 0;
-    if (e != hipSuccess || side_refresh(d) != hipSuccess || curved_refresh(d) != hipSuccess ||
-        hipStreamSynchronize(d->stream) != hipSuccess)
+    if (side_refresh(d) != hipSuccess || curved_refresh(d) != hipSuccess ||
+        hipStreamSynchronize(d->stream) != hipSuccess) {
+        d->unstable = true;
         return fail(LBM_ERR_DEVICE, "population import failed");
+    }
     return LBM_OK;
 }
 
@@ -1358,9 +1381,9 @@ int lbm_save_state(lbm_domain *d, void *buf, size_t bytes)
     state_header(d, h);
     std::memcpy(buf, h, sizeof h);
     char *p = (char *)buf + kStateHeader;
-    if (copy_out(d, p, d->buf, d->bytes) != hipSuccess || copy_out(d, p + d->bytes, d->d_bzaux, aux) != hipSuccess)
-        return fail(LBM_ERR_DEVICE, "state download failed");
-    return LBM_OK;
+    if (int rc = moved_out(copy_out(d, p, d->buf, d->bytes), "state download"))
+        return rc;
+    return moved_out(copy_out(d, p + d->bytes, d->d_bzaux, aux), "state download");
 }
 
 int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes)
@@ -1389,9 +1412,12 @@ int lbm_load_state(lbm_domain *d, const void *buf, size_t bytes)
         return fail(LBM_ERR_ARG, "state image of %zu bytes; its header gives %llu", bytes,
                     (unsigned long long)(kStateHeader + h[2] + h[3]));
     const char *p = (const char *)buf + kStateHeader;
-    if (copy_in(d, d->buf, p, d->bytes) != hipSuccess || copy_in(d, d->d_bzaux, p + d->bytes, h[3]) != hipSuccess ||
-        hipStreamSynchronize(d->stream) != hipSuccess)
-        return fail(LBM_ERR_DEVICE, "state upload failed");
+    if (int rc = moved_in(d, copy_in(d, d->buf, p, d->bytes), "state upload"))
+        return rc;
+    d->unstable = true; // until the new state is complete
+    if (int rc = moved_in(d, copy_in(d, d->d_bzaux, p + d->bytes, h[3]), "state upload"))
+        return rc;
+    HIP_TRY(hipStreamSynchronize(d->stream));
     d->phase = (int)(h[5] & 1u);
     if (int rc = clear_status(d))
         return rc;
@@ -1447,11 +1473,12 @@ int lbm_stats_get(lbm_domain *d, double *mean_u, double *mean_uu, double *mean_s
         if (hipGetLastError() != hipSuccess)
             rc = fail(LBM_ERR_DEVICE, "statistics export failed");
     }
-    if (rc == LBM_OK &&
-        (copy_out(d, mean_u, dout, 3 * n * sizeof(double)) != hipSuccess ||
-         copy_out(d, mean_uu, dout + 3 * n, 6 * n * sizeof(double)) != hipSuccess ||
-         copy_out(d, mean_sigma, dout + 9 * n, 6 * n * sizeof(double)) != hipSuccess))
-        rc = fail(LBM_ERR_DEVICE, "statistics download failed");
+    if (rc == LBM_OK)
+        rc = moved_out(copy_out(d, mean_u, dout, 3 * n * sizeof(double)), "statistics download");
+    if (rc == LBM_OK)
+        rc = moved_out(copy_out(d, mean_uu, dout + 3 * n, 6 * n * sizeof(double)), "statistics download");
+    if (rc == LBM_OK)
+        rc = moved_out(copy_out(d, mean_sigma, dout + 9 * n, 6 * n * sizeof(double)), "statistics download");
     dfree(d->stream, dout);
     return rc;
 }
