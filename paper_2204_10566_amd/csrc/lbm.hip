@@ -13,6 +13,7 @@
 #include <cstdarg>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <map>
