@@ -280,9 +280,10 @@ int lbm_step_wait(lbm_domain *d);
 
 /*
  * Build the step graph now: a chain of 64 step kernels that runs of 64
- * steps and more replay.  Without this call the first run of at least 256
- * steps after a change of rates, outlet, walls, statistics or equilibrium
- * order builds it; shorter runs launch their steps one by one.  Lets a
+ * steps and more replay.  Without this call a run of 64 steps or more
+ * builds it once 256 steps have been asked for since the last change of
+ * rates, outlet, walls, statistics or equilibrium order; until then, and in
+ * shorter runs, the steps are launched one by one.  Lets a
  * caller keep the building (about 0.1 ms) out of a timed run.  Errors:
  * LBM_ERR_STATE for a domain resident in a batch, LBM_ERR_DEVICE.
  */
