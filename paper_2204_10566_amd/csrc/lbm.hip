@@ -694,16 +694,20 @@ int build_tables(lbm_domain *d, const uint8_t *flags)
     return LBM_OK;
 }
 
-// Host copies of the tile list and, per lane of the wall tiles, the link
-// masks and the inlet links.
-int host_tables(const lbm_domain *d, std::vector<TileRec> &tiles, std::vector<uint32_t> &wall,
-                std::vector<uint32_t> &inlm)
+// Host copies of the tile list ...
+int host_tiles(const lbm_domain *d, std::vector<TileRec> &tiles)
 {
     tiles.resize(d->ntiles);
+    HIP_TRY(copy_sync(d->stream, tiles.data(), d->d_tiles, tiles.size() * sizeof(TileRec), hipMemcpyDeviceToHost));
+    return LBM_OK;
+}
+
+// ... and, per lane of the wall tiles, of the link masks and the inlet links.
+int host_links(const lbm_domain *d, std::vector<uint32_t> &wall, std::vector<uint32_t> &inlm)
+{
     wall.resize(d->nwall * 64);
     inlm.resize(d->nwall * 64);
     std::vector<uint32_t> rec(d->n_inlrec * kRecWords);
-    HIP_TRY(copy_sync(d->stream, tiles.data(), d->d_tiles, tiles.size() * sizeof(TileRec), hipMemcpyDeviceToHost));
     HIP_TRY(copy_sync(d->stream, wall.data(), d->d_wall, wall.size() * 4, hipMemcpyDeviceToHost));
     HIP_TRY(copy_sync(d->stream, inlm.data(), d->d_inlet, inlm.size() * 4, hipMemcpyDeviceToHost));
     HIP_TRY(copy_sync(d->stream, rec.data(), d->d_inlrec, rec.size() * 4, hipMemcpyDeviceToHost));
@@ -991,14 +995,20 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
         return rc;
     if (d->batch)
         return fail(LBM_ERR_STATE, "domain is resident in a batch");
+    if (!q && !d->curved()) { // the halfway rule, as it is
+        HIP_TRY(normalise(d));
+        return LBM_OK;
+    }
     const size_t nco = (size_t)d->nwall * Q * 64;
     std::vector<TileRec> tiles;
-    std::vector<uint32_t> wall, inlm;
-    if (int rc = host_tables(d, tiles, wall, inlm))
+    if (int rc = host_tiles(d, tiles))
         return rc;
     std::vector<float> coef;
     std::vector<uint32_t> bz(tiles.size(), 0u), bzf(tiles.size(), 0u);
     if (q) {
+        std::vector<uint32_t> wall, inlm;
+        if (int rc = host_links(d, wall, inlm))
+            return rc;
         coef.assign(nco, 1.f);
         for (size_t t = 0; t < tiles.size(); ++t) {
             const TileRec &r = tiles[t];
