@@ -1004,7 +1004,7 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
     if (int rc = host_tiles(d, tiles))
         return rc;
     std::vector<float> coef;
-    std::vector<uint32_t> bz(tiles.size(), 0u), bzf(tiles.size(), 0u);
+    std::vector<uint32_t> bz(tiles.size(), 0u), far(tiles.size(), 0u);
     if (q) {
         std::vector<uint32_t> wall, inlm;
         if (int rc = host_links(d, wall, inlm))
@@ -1032,7 +1032,7 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
                     const bool near = qq < 0.5;
                     const float a = (float)(near ? 2.0 * qq : 1.0 / (2.0 * qq));
                     coef[((size_t)r.wall * Q + k) * 64 + l] = near ? a : -a;
-                    bzf[t] |= near ? 0u : 1u << k;
+                    far[t] |= near ? 0u : 1u << k;
                     bz[t] |= 1u << k;
                 }
             }
@@ -1061,7 +1061,7 @@ int lbm_set_wall_distances(lbm_domain *d, const float *q)
     }
     for (size_t t = 0; t < bz.size(); ++t) {
         tiles[t].bz = bz[t];
-        tiles[t].bzf = bzf[t];
+        tiles[t].edge = (tiles[t].edge & kEdge) | far[t];
     }
     HIP_TRY(copy_sync(d->stream, d->d_tiles, tiles.data(), tiles.size() * sizeof(TileRec), hipMemcpyHostToDevice));
     if (any) {

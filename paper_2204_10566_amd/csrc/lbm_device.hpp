@@ -144,9 +144,11 @@ struct KDomain {
     uint32_t feq_order;      // 2..5: explicit equilibrium truncated at that order (variant kVarFeq); 6: full
 };
 
-// One entry of a tile list (44 bytes; a wave reads it with scalar loads).
+// One entry of a tile list (40 bytes; a wave reads it with scalar loads).
 // An interior tile needs nothing else; a wall tile adds one 32-bit link
-// mask per lane (KDomain::wall).
+// mask per lane (KDomain::wall).  It stays at 40: with an eleventh word, FP32
+// steps of periodic boxes, bound by memory, took 1 % more (256^3 673 -> 680 us
+// a step, 192^3 293 -> 295).
 struct TileRec {
     uint32_t slot;   // domain slot in a packed launch (0 otherwise)
     uint32_t tile;   // cells [64 tile, 64 tile + 64)
@@ -154,12 +156,16 @@ struct TileRec {
     uint32_t inl;    // inlet-term block, kNoRec if no cell has an inlet link
     uint32_t inlm;   // union of the cells' inlet links
     uint32_t act[2]; // bit l of act[l / 32]: the cell of lane l is updated
-    uint32_t edge;   // 1: an updated cell of the tile lies on the outlet plane x = nx - 1
+    uint32_t edge;   // kEdge: an updated cell of the tile lies on the outlet plane x = nx - 1; and far_links
     uint32_t ord;    // position of the tile in its domain's tile list
     uint32_t bz;     // links with a curved-wall coefficient in some cell of the tile
-    uint32_t bzf;    // of these, links at a wall fraction > 1/2 in some cell
 };
-static_assert(sizeof(TileRec) == 44, "tile record layout");
+static_assert(sizeof(TileRec) == 40, "tile record layout");
+constexpr uint32_t kEdge = 1u << 31;
+__host__ __device__ inline bool on_edge(const TileRec &rec) { return (rec.edge & kEdge) != 0u; }
+// Of the links with a curved-wall coefficient, those at a wall fraction > 1/2
+// in some cell of the tile.
+__host__ __device__ inline uint32_t far_links(const TileRec &rec) { return rec.edge & ~kEdge; }
 
 // Tile-major population layout: the 27 populations of the 64 cells of a
 // tile are one contiguous block, population i of the cell in lane l at
@@ -958,7 +964,7 @@ __device__ __forceinline__ void curved_walls(const KDomain &d, const TileRec &re
             x[j] = 0.f;
             if ((rec.bz >> k) & 1u)
                 a[j] = d.bzc[base + k * 64u];
-            if ((rec.bzf >> k) & 1u)
+            if ((far_links(rec) >> k) & 1u)
                 x[j] = d.bzaux[base + k * 64u];
         }
 #pragma unroll
@@ -978,7 +984,7 @@ __device__ __forceinline__ void curved_keep(const KDomain &d, const TileRec &rec
     const size_t base = (size_t)(uint32_t)rec.wall * (Q * 64u) + lane;
 #pragma unroll
     for (int k = 0; k < Q; ++k)
-        if ((rec.bzf >> k) & 1u)
+        if ((far_links(rec) >> k) & 1u)
             d.bzaux[base + k * 64u] = f[k];
 }
 
@@ -1347,7 +1353,7 @@ __device__ __forceinline__ void local_finish(const KDomain &d, const TileRec &re
         for (int c = 0; c < 15; ++c)
             acc[(size_t)c * d.sstride] += v[c];
     }
-    if (rec.edge) {
+    if (on_edge(rec)) {
         const uint32_t q = fdiv(lin, d.dnx);
         if (lin - q * d.nx == d.nx - 1u) {
             // last-plane cell: its c_x = -1 values for the outlet cells
@@ -1437,12 +1443,12 @@ __global__ __launch_bounds__(kBlock) void k_stream_collide(KDomain d, const Tile
     for (uint32_t t = w0; t < ntiles; t += nw) {
         const TileRec rec = tiles[t];
         if constexpr (ROWS) {
-            if (rec.edge)
+            if (on_edge(rec))
                 stream_tile_rows<ST, V, true, false, W64>(d, rec, lane);
             else
                 stream_tile_rows<ST, V, false, false, W64>(d, rec, lane);
         } else {
-            if (rec.edge)
+            if (on_edge(rec))
                 stream_tile_t<ST, V, true, false, W64>(d, rec, lane);
             else
                 stream_tile_t<ST, V, false, false, W64>(d, rec, lane);
@@ -1499,12 +1505,12 @@ __global__ __launch_bounds__(kBlock, (kBatchedMinBlocks<V, PHASE>)) void k_colli
             continue;
         if constexpr (PHASE == 0u) {
             if constexpr (ROWS) {
-                if (rec.edge)
+                if (on_edge(rec))
                     stream_tile_rows<ST, V, true, true>(dd, rec, lane);
                 else
                     stream_tile_rows<ST, V, false, true>(dd, rec, lane);
             } else {
-                if (rec.edge)
+                if (on_edge(rec))
                     stream_tile_t<ST, V, true, true>(dd, rec, lane);
                 else
                     stream_tile_t<ST, V, false, true>(dd, rec, lane);
@@ -1553,7 +1559,7 @@ __global__ __launch_bounds__(256) void k_normalise(KDomain d, const TileRec *__r
     const Coords C = coords(d, lin);
     const uint64_t self = cell_bytes<es, uint64_t>(lin, d.tbytes);
     const uint32_t m = rec.wall >= 0 ? d.wall[(uint32_t)rec.wall * 64u + lane] : 0u;
-    const bool edge_lane = rec.edge && C.x == d.nx - 1u;
+    const bool edge_lane = on_edge(rec) && C.x == d.nx - 1u;
     for (int k = 0; k < Q; ++k) {
         if ((m >> k) & 1u) {
             if ((rec.inlm >> k) & 1u) {
@@ -1626,14 +1632,14 @@ __global__ __launch_bounds__(256) void k_curved_refresh(KDomain d, const TileRec
     if (t >= ntiles)
         return;
     const TileRec rec = tiles[t];
-    if (rec.wall < 0 || !rec.bzf || !lane_active(rec, lane))
+    if (rec.wall < 0 || !far_links(rec) || !lane_active(rec, lane))
         return;
     const Pops<ST, true> r(d);
     const uint64_t self = cell_bytes<es, uint64_t>(rec.tile * 64u + lane, d.tbytes);
     float f[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k)
-        f[k] = ((rec.bzf >> k) & 1u) ? r.load(self, pop_bytes<es>(Q - 1 - k), k) : 0.f;
+        f[k] = ((far_links(rec) >> k) & 1u) ? r.load(self, pop_bytes<es>(Q - 1 - k), k) : 0.f;
     curved_keep(d, rec, lane, f);
 }
 
