@@ -112,9 +112,10 @@ uint64_t array_bytes(uint64_t P, int ny, int nz, int storage)
 // Status words of domains: 4 bytes each of pinned host memory that the first
 // unstable waves write (check_state), so that waiting for steps is one stream
 // synchronisation and a host read, with no copy behind it (one step of a 16^3
-// box, waited for: 34.8 -> 14.5 us).  The words come from blocks of 1024; a
-// block is given back when none of its words is in use and another block is
-// left.
+// box, waited for: 34.8 -> 14.5 us).  The words come from blocks of 1024.
+// Pinned memory is given back (give_back_pinned) only where the library waits
+// for the device anyway: hipHostFree waits for all work on it, other
+// libraries' included, and a domain is destroyed beside that.
 struct StatusWord {
     uint32_t *host = nullptr, *dev = nullptr;
 };
@@ -169,13 +170,20 @@ void status_free(StatusWord &w)
         if (w.host < b.host || w.host >= b.host + kStatusBlockWords)
             continue;
         b.unused.push_back((uint32_t)(w.host - b.host));
-        if (b.unused.size() == kStatusBlockWords && g_status_blocks.size() > 1) {
-            (void)hipHostFree(b.host);
-            g_status_blocks.erase(g_status_blocks.begin() + (ptrdiff_t)k);
-        }
         break;
     }
     w = StatusWord{};
+}
+
+// Frees the blocks without a word in use, but one.
+void status_give_back()
+{
+    std::lock_guard<std::mutex> lock(g_status_mutex);
+    for (size_t k = g_status_blocks.size(); k-- > 0 && g_status_blocks.size() > 1;)
+        if (g_status_blocks[k].unused.size() == kStatusBlockWords) {
+            (void)hipHostFree(g_status_blocks[k].host);
+            g_status_blocks.erase(g_status_blocks.begin() + (ptrdiff_t)k);
+        }
 }
 
 // What the host knows of a status word once the steps are complete.
@@ -189,7 +197,6 @@ struct lbm_domain {
     uint64_t ncells = 0, P = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    bool in_ring = false; // counted among the users of its device's pinned chunks
     bool own_buffers = true;
     int device = 0;
     char *buf = nullptr;  // the population array
@@ -387,8 +394,6 @@ void release_graph(lbm_domain *d)
     d->graph_dirty = true;
 }
 
-void ring_leave(int device);
-
 void free_domain(lbm_domain *d)
 {
     release_graph(d);
@@ -404,8 +409,6 @@ void free_domain(lbm_domain *d)
             (void)hipStreamDestroy(s);
     }
     status_free(d->status);
-    if (d->in_ring)
-        ring_leave(d->device);
     delete d;
 }
 
@@ -758,7 +761,6 @@ int create(const uint8_t *flags, int nx, int ny, int nz, unsigned periodic, int 
     };
     if (hipGetDevice(&d->device) != hipSuccess)
         return bail(fail(LBM_ERR_DEVICE, "no HIP device"));
-    d->in_ring = ring_join(d->device);
     if (hip_stream) {
         d->stream = (hipStream_t)hip_stream;
     } else {
