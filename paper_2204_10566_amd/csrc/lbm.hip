@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cstdarg>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <condition_variable>
 #include <cstdio>
