@@ -1268,11 +1268,22 @@ __device__ __forceinline__ void stream_tile_rows(const KDomain &d, const TileRec
     // unrolled loop the compiler left 27 of them, 64 branches and 240 scalar
     // instructions per interior wave.  FP16S streaming step of a periodic
     // 128^3 box 45.5 -> 41.5 us (226 MB, 5.0 -> 5.5 TB/s), of the 96 x 96 x
-    // 768 nozzle 31.1 -> 29.6 us.
+    // 768 nozzle 31.1 -> 29.6 us.  Without the branches between them the FP32
+    // stores of a wave came too close together for device memory: steps of
+    // periodic boxes beyond the last-level cache took 0.5 to 1 % longer (320^3
+    // 1340 -> 1353 us, 192^3 291 -> 293).  Sixteen idle cycles after each give
+    // that back (1337, 290.5) and cost nothing where the cache takes them
+    // (128^3 64.5 -> 64.6, the FP32 nozzle 37.4 -> 37.2); with 32, 128^3 loses.
     if (!wall) {
 #pragma unroll
-        for (int k = 0; k < Q; ++k)
+        for (int k = 0; k < Q; ++k) {
             r.store(A.xo[k % 3], A.row[k / 3] + pop_bytes<es>(Q - 1 - k), f[Q - 1 - k], k);
+            if constexpr (es == 4) {
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_nop 15");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
     } else {
         const Off self2 = (Off)rec.tile * d.tbytes + lane2 * es;
 #pragma unroll
