@@ -220,7 +220,7 @@ int lbm_set_equilibrium_order(lbm_domain *d, int order);
  *        q >= 1/2: f_i(x) = f*_ibar(x)/(2q) + (1 - 1/(2q)) f*_i(x)
  *      q = 1/2 is the halfway rule; so is q < 1/2 when the link x -> x + c_i
  *      is not a plain link (a gap one cell wide, an inlet behind it).
- * Takes effect at the next step; the state is kept.  Device memory: 12 bytes
+ * Takes effect at the next step; the state is kept.  Device memory: 8 bytes
  * per link slot of the wall tiles (27*64 per wall tile), only while some q
  * differs from 1/2.  Errors: LBM_ERR_ARG for a fraction outside (0, 1] at a
  * wall link (nothing changed), LBM_ERR_STATE for a domain resident in a

@@ -1487,9 +1487,12 @@ __global__ __launch_bounds__(kBlock) void k_local_collide(KDomain d, const TileR
 // tile belongs to one domain, whose descriptor says whether it takes part
 // in this step.  The streaming kernel of the reduced collision without
 // curved walls is bounded to six waves per SIMD: left alone the compiler
-// takes 81 VGPRs (five waves) for FP16S, bounded 72, with no spills (packed
-// steps 0.7 % faster); the curved-wall variants would spill under the same
-// bound.
+// takes 81 VGPRs (five waves) for BF16S with general addressing, bounded 80
+// with no spills; FP16S takes 78 and FP32 65 either way.  (An earlier FP16S
+// kernel took 81 and 72, and packed steps were 0.7 % faster bounded.)  The
+// curved-wall variants would spill under the same bound, and the stand-alone
+// FP16S kernel of the same addressing, which takes 81, is slower under it:
+// the 96 x 96 x 750 nozzle 26.0 -> 27.9 us a step.
 template <int V, uint32_t PHASE>
 constexpr int kBatchedMinBlocks = ((V & kVarH1) != 0 && (V & kVarCurved) == 0 && PHASE == 0u) ? 6 : 1;
 
