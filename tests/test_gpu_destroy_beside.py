@@ -40,14 +40,16 @@ def test_destroy_beside_other_work(capi):
     each = (time.perf_counter() - t) / 40
     beside = []
     # a stream may share a hardware queue with the other work and then waits
-    # for it in any case: another domain's does not
-    while len(beside) < 6 and not any(beside):
-        d = capi.Domain(I.periodic_box(80), periodic=7)
+    # for it in any case: not every one of eight does
+    for stream in [torch.cuda.Stream() for _ in range(8)]:
+        d = capi.Domain(I.periodic_box(80), periodic=7, stream=stream.cuda_stream)
         d.populations()  # 55 MB
         done = products(int(0.25 / each))  # a quarter of a second of them
         d.destroy()
         beside.append(not done.query())
         done.synchronize()
+        if beside[-1]:
+            break
     assert any(beside)
 
 
